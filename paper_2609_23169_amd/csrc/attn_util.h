@@ -110,6 +110,17 @@ __device__ inline void buffer_load_lds16(__amdgpu_buffer_rsrc_t rs, char* lds, i
                                            voffset, 0, 0, 0);
 }
 
+// Tile (b, h, block) = bh nblk + block of this workgroup. Plain order, or with
+// by_head (heads a multiple of 8) each head's tiles on one XCD: workgroups go
+// round-robin to the 8 XCDs, so workgroup 8 k + x is the k-th of XCD x and
+// takes tile k of the heads x, x + 8, ...
+__device__ inline int64_t tile_index(bool by_head, int nblk) {
+  const unsigned wg = blockIdx.x;
+  if (!by_head) return wg;
+  const unsigned k = wg >> 3;
+  return (int64_t)((k / nblk) * 8 + (wg & 7)) * nblk + k % nblk;
+}
+
 // Where sample b's rows live. Uniform batch (cu == nullptr): tokens
 // [b N, b N + N) of the packed [B N, H, D] tensors, per-row statistics (LSE
 // and its relatives) laid out [B, H, N]. Variable lengths: tokens

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), (BLOCK == 128 || D == 64) ? 2 : 
     const __bf16* __restrict__ dO, const float* __restrict__ aux, __bf16* __restrict__ dQ, int B,
     int N_all, int H, int nblk, float scale, const int32_t* __restrict__ rowptr,
     const int32_t* __restrict__ cols, const int32_t* __restrict__ cu_seqlens, int64_t T_tok,
-    const int32_t* __restrict__ row_ok) {
+    const int32_t* __restrict__ row_ok, bool by_head) {
   using C = BwdCfg<D, BLOCK, BLOCK / 32>;
   __shared__ __attribute__((aligned(1024))) char k_lds0[C::TILEB];
   __shared__ __attribute__((aligned(1024))) char k_lds1[C::TILEB];
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), (BLOCK == 128 || D == 64) ? 2 : 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  const int64_t lt = blockIdx.x;   // tile order: see the launcher
+  const int64_t lt = tile_index(by_head, nblk);   // tile order: see the launcher
   if (row_ok && row_ok[lt]) return;   // dQ comes from the stored dS tiles
   const int i = (int)(lt % nblk);
   const int64_t bh = lt / nblk;
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dq_stored_kernel(
     const __bf16* __restrict__ K, const char* __restrict__ ds, __bf16* __restrict__ dQ,
     int N_all, int H, int nblk, float scale, const int32_t* __restrict__ rowptr,
     const int32_t* __restrict__ cols, const int32_t* __restrict__ cu_seqlens, int64_t T_tok,
-    const int32_t* __restrict__ map, const int32_t* __restrict__ row_ok) {
+    const int32_t* __restrict__ map, const int32_t* __restrict__ row_ok, bool by_head) {
   constexpr int NW = BLOCK / 32;
   using C = BwdCfg<D, BLOCK, NW>;
   constexpr int PAIRB = 2 * BLOCK * BLOCK;   // one pair's dS tile
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dq_stored_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t lt = blockIdx.x;
+  const int64_t lt = tile_index(by_head, nblk);
   if (!row_ok[lt]) return;   // not all stored: the recompute pass takes it
   const int p0 = rowptr[lt], pe = rowptr[lt + 1];
   const int i = (int)(lt % nblk);
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
     __bf16* __restrict__ dV, int B, int N_all, int H, int nblk, float scale,
     const int32_t* __restrict__ colptr, const int32_t* __restrict__ rows_list,
     const int32_t* __restrict__ cu_seqlens, int64_t T_tok, char* __restrict__ ds,
-    int64_t max_pairs) {
+    int64_t max_pairs, bool by_head) {
   constexpr int NK = BLOCK / 32;        // key groups (one wave each)
   using C = BwdCfg<D, BLOCK, NK, 32>;
   constexpr int AUXB = 2048;            // 32 rows of each plane, one 1 KB load each
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kw = w;   // 32-key group
   const int l32 = lane & 31, g = lane >> 5;
-  const int64_t lt = blockIdx.x;   // tile order: see the launcher
+  const int64_t lt = tile_index(by_head, nblk);   // tile order: see the launcher
   const int j = (int)(lt % nblk);
   const int64_t bh = lt / nblk;
   const int h = (int)(bh % H), b = (int)(bh / H);
@@ -763,10 +763,12 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
                         hipStream_t s) {
   auto bf = [](const void* p) { return static_cast<const __bf16*>(p); };
   const int64_t rows_total = sh.T * sh.H * (D / 8);
-  // One workgroup per (b, h, block) in plain order. Workgroups go round-robin
-  // to the 8 XCDs, so all XCDs work on the same few heads at once (their K and
-  // V stay in the shared last-level cache) and a run of heavy blocks is spread
-  // over every XCD.
+  // One workgroup per (b, h, block), in plain order where a head's tensors are
+  // large: workgroups go round-robin to the 8 XCDs, so all XCDs work on the
+  // same few heads at once (their tensors stay in the shared last-level cache)
+  // and a run of heavy blocks is spread over every XCD. Small heads go to one
+  // XCD each (heads_by_xcd).
+  const bool by_head = heads_by_xcd(sh);
   const int64_t nrow = (int64_t)sh.B * sh.H * sh.nblk;
   const dim3 grid((unsigned)nrow);
   const bool store = ds.max_pairs > 0 && ds.tiles && ds.map && ds.row_ok;
@@ -785,19 +787,19 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
     hipLaunchKernelGGL((bwd_dkdv_kernel<D, BLOCK, true>), grid, dim3(64 * (BLOCK / 32)), 0, s,
                      bf(q), bf(k), bf(v), bf(dout), aux, static_cast<__bf16*>(dk),
                      static_cast<__bf16*>(dv), sh.B, sh.N, sh.H, sh.nblk, sh.scale, colptr, rows,
-                     sh.cu, sh.T, ds.tiles, ds.max_pairs);
+                     sh.cu, sh.T, ds.tiles, ds.max_pairs, by_head);
   } else {
     TraceScope ts_(s, "bwd_dkdv", D, BLOCK);
     hipLaunchKernelGGL((bwd_dkdv_kernel<D, BLOCK, false>), grid, dim3(64 * (BLOCK / 32)), 0, s,
                      bf(q), bf(k), bf(v), bf(dout), aux, static_cast<__bf16*>(dk),
                      static_cast<__bf16*>(dv), sh.B, sh.N, sh.H, sh.nblk, sh.scale, colptr, rows,
-                     sh.cu, sh.T, static_cast<char*>(nullptr), (int64_t)0);
+                     sh.cu, sh.T, static_cast<char*>(nullptr), (int64_t)0, by_head);
   }
   if (store) {
     TraceScope ts_(s, "bwd_dq_stored", D, BLOCK);
     hipLaunchKernelGGL((bwd_dq_stored_kernel<D, BLOCK>), grid, dim3(64 * (BLOCK / 32)), 0, s,
                      bf(k), static_cast<const char*>(ds.tiles), static_cast<__bf16*>(dq), sh.N, sh.H,
-                     sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T, ds.map, ds.row_ok);
+                     sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T, ds.map, ds.row_ok, by_head);
   }
   {
     // every query block without row_ok (all of them without stored tiles)
@@ -805,7 +807,7 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
     hipLaunchKernelGGL((bwd_dq_kernel<D, BLOCK>), grid, dim3(64 * (BLOCK / 32)), 0, s,
                      bf(q), bf(k), bf(v), bf(dout), aux, static_cast<__bf16*>(dq), sh.B, sh.N, sh.H,
                      sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T,
-                     store ? static_cast<const int32_t*>(ds.row_ok) : nullptr);
+                     store ? static_cast<const int32_t*>(ds.row_ok) : nullptr, by_head);
   }
   return hipGetLastError();
 }

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), (BLOCK == 128 || D == 64) ? 2 : 
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     __bf16* __restrict__ O, float* __restrict__ LSE, int B, int N_all, int H, int nblk, float scale,
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ cols,
-    const int32_t* __restrict__ cu_seqlens, int64_t T_tok) {
+    const int32_t* __restrict__ cu_seqlens, int64_t T_tok, bool by_head) {
   using C = FwdCfg<D, BLOCK>;
   // Four LDS objects (K and V, two stages each): distinct objects let the
   // compiler see that a load into one never aliases reads of another.
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), (BLOCK == 128 || D == 64) ? 2 : 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, uniform
   const int l32 = lane & 31, g = lane >> 5;
-  const int64_t lt = blockIdx.x;   // tile order: see the launcher
+  const int64_t lt = tile_index(by_head, nblk);   // tile order: see the launcher
   const int i = (int)(lt % nblk);
   const int64_t bh = lt / nblk;
   const int h = (int)(bh % H), b = (int)(bh / H);
@@ -366,17 +366,18 @@ template <int D, int BLOCK>
 hipError_t launch_fwd_t(const void* q, const void* k, const void* v, void* o, float* lse,
                         const AttnShape& sh, const int32_t* rowptr, const int32_t* cols,
                         hipStream_t s) {
-  // One workgroup per (b, h, block) in plain order. Workgroups go round-robin
-  // to the 8 XCDs, so all XCDs work on the same few heads at once (their K and
-  // V stay in the shared last-level cache) and a run of heavy blocks is spread
-  // over every XCD.
+  // One workgroup per (b, h, block), in plain order where a head's K and V are
+  // large: workgroups go round-robin to the 8 XCDs, so all XCDs work on the
+  // same few heads at once (their K and V stay in the shared last-level cache)
+  // and a run of heavy blocks is spread over every XCD. Small heads go to one
+  // XCD each (heads_by_xcd).
   const dim3 grid((unsigned)((int64_t)sh.B * sh.H * sh.nblk));
   {
     TraceScope ts_(s, "bsattn_fwd", D, BLOCK);
     hipLaunchKernelGGL((bsattn_fwd_kernel<D, BLOCK>), grid, dim3(FwdCfg<D, BLOCK>::NT), 0,
                      s, static_cast<const __bf16*>(q), static_cast<const __bf16*>(k),
                      static_cast<const __bf16*>(v), static_cast<__bf16*>(o), lse, sh.B, sh.N, sh.H,
-                     sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T);
+                     sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T, heads_by_xcd(sh));
   }
   return hipGetLastError();
 }

@@ -63,6 +63,21 @@ struct AttnShape {
   const int32_t* cu = nullptr;   // [B + 1] sample offsets, or null for a uniform batch
   int64_t T = 0;                 // packed tokens (B N when uniform)
 };
+// Whether the attention kernels give each XCD whole heads (tile_index) or take
+// the tiles in plain order, all XCDs on the same heads. A workgroup streams
+// two [N, D] tensors of its head (K and V, or Q and dO): with whole heads an
+// XCD's workgroups share them in its own 4 MiB of L2, in plain order every
+// XCD reads every head from the last-level cache behind the L2s. Measured in
+// ms, plain / by head: forward at 24 x 6,552 x 128 (3.4 MB a head) 0.181 /
+// 0.169, dK/dV at 32 x 9,011 x 64 (2.3 MB) 0.312 / 0.303, dense forward at
+// 24 x 12,801 x 128 (6.6 MB) 1.91 / 1.89, but forward at 24 x 77,586 x 128
+// (39 MB) 7.05 / 7.52 and dK/dV there 13.4 / 13.9: eight heads at once then
+// overflow the last-level cache too. The head count has to divide by 8 so
+// that every XCD gets as many heads of every sample.
+constexpr int64_t kXcdHeadBytes = (int64_t)8 << 20;
+inline bool heads_by_xcd(const AttnShape& sh) {
+  return sh.H % 8 == 0 && (int64_t)sh.N * sh.D * 4 <= kXcdHeadBytes;
+}
 hipError_t launch_bsattn_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
                              const AttnShape& sh, const int32_t* rowptr, const int32_t* cols,
                              hipStream_t s);
