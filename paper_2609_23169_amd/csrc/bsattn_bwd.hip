@@ -1,7 +1,7 @@
 // Block-sparse attention backward on gfx950: gradients of Eq. 8 (paper
 // Sec. 3.3) with the block mask held constant. No atomics, deterministic.
-// Three launches with the minimum workspace (five when it holds dS tiles,
-// below):
+// Three launches with the minimum workspace (two at head_dim 64, where dQ goes
+// first and does the pre-pass's work; five when it holds dS tiles, below):
 //
 //   prep  : per query row, LSE log2(e) and -delta = -sum_d dO[r,d] O[r,d]
 //           (fp32, two planes of the workspace);
@@ -165,13 +165,17 @@ __global__ __launch_bounds__(64) void bwd_ds_map_kernel(
 // ---------------------------------------------------------------------------
 // dQ: query-stationary over the row lists
 // ---------------------------------------------------------------------------
-template <int D, int BLOCK>
+// With DELTA the pass runs first, forms LSE log2 e and -delta of its own rows
+// from LSE, O and the dO operands it holds anyway, and writes both planes for
+// the dK/dV pass: no pre-pass launch and no second read of dO.
+template <int D, int BLOCK, bool DELTA>
 __global__ __launch_bounds__(64 * (BLOCK / 32), (BLOCK == 128 || D == 64) ? 2 : 1) void bwd_dq_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
-    const __bf16* __restrict__ dO, const float* __restrict__ aux, __bf16* __restrict__ dQ, int B,
+    const __bf16* __restrict__ dO, float* __restrict__ aux, __bf16* __restrict__ dQ, int B,
     int N_all, int H, int nblk, float scale, const int32_t* __restrict__ rowptr,
     const int32_t* __restrict__ cols, const int32_t* __restrict__ cu_seqlens, int64_t T_tok,
-    const int32_t* __restrict__ row_ok, bool by_head) {
+    const int32_t* __restrict__ row_ok, bool by_head, const __bf16* __restrict__ O,
+    const float* __restrict__ LSE) {
   using C = BwdCfg<D, BLOCK, BLOCK / 32>;
   __shared__ __attribute__((aligned(1024))) char k_lds0[C::TILEB];
   __shared__ __attribute__((aligned(1024))) char k_lds1[C::TILEB];
@@ -205,132 +209,158 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), (BLOCK == 128 || D == 64) ? 2 : 
 #pragma unroll
   for (int dt = 0; dt < DT16; ++dt) dq16[dt][0] = dq16[dt][1] = f32x4{};
 
-  if (T > 0) {
+  // With DELTA also a query block without pairs writes its statistics.
+  if (DELTA || T > 0) {
     bf16x8 qop[C::KS], doop[C::KS];
-    {
-      const int64_t off = base_bh + (int64_t)min(q, N - 1) * tok_stride + 8 * g;
+    const int64_t off = base_bh + (int64_t)min(q, N - 1) * tok_stride + 8 * g;
 #pragma unroll
-      for (int ks = 0; ks < C::KS; ++ks) {
-        qop[ks] = *reinterpret_cast<const bf16x8*>(Q + off + 16 * ks);
-        doop[ks] = *reinterpret_cast<const bf16x8*>(dO + off + 16 * ks);
-      }
+    for (int ks = 0; ks < C::KS; ++ks) {
+      qop[ks] = *reinterpret_cast<const bf16x8*>(Q + off + 16 * ks);
+      doop[ks] = *reinterpret_cast<const bf16x8*>(dO + off + 16 * ks);
     }
     const int64_t ar = sr.stat0 + min(q, N - 1);
-    const float lse2 = aux[ar], ndl = aux[(int64_t)H * T_tok + ar];   // LSE log2 e, -delta
-    const LaneOffsets<C> lo(w, lane, tok_stride);
-    // K^T operand of the 16x16x32 dQ product for d tile dt, key step kc:
-    // lane group gq reads key rows 32 kc + base(gq) + (c16 >> 2) (slots
-    // 0..3) and the same + 16 (slots 4..7), columns 16 dt + 4 (c16 & 3) .. +3,
-    // base(gq) = 8 (gq & 1) + 4 (gq >> 1): the keys the dS exchange leaves in
-    // that lane group.
-    int ktr[DT16];
+    float lse2, ndl;   // LSE log2 e, -delta
+    if constexpr (DELTA) {
+      // the pre-pass's order of additions: 8 elements each, then chunks
+      // 4, 2 and 1 apart (chunk 2 ks + g)
+      float part[C::KS];
 #pragma unroll
-    for (int dt = 0; dt < DT16; ++dt) {
-      const int d = 16 * dt + 4 * (c16 & 3);
-      ktr[dt] = lds_off<C::CPR>(8 * (gq & 1) + 4 * (gq >> 1) + (c16 >> 2), d >> 3) + 2 * (d & 7);
-    }
-
-    auto load_tile = [&](const __bf16* X, int t, char* dst) __attribute__((always_inline)) {
-      const int j = cols[p0 + t / C::SUBS];
-      const int key0 = j * BLOCK + (t % C::SUBS) * C::ST;
-      const int nrec = key0 < N ? (N - key0 - 1) * (int)(tok_stride * 2) + 2 * D : 0;
-      const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(X + base_bh + (int64_t)key0 * tok_stride, nrec);
+      for (int ks = 0; ks < C::KS; ++ks) {
+        const bf16x8 o = *reinterpret_cast<const bf16x8*>(O + off + 16 * ks);
+        part[ks] = 0.f;
 #pragma unroll
-      for (int u = 0; u < C::IPW; ++u) buffer_load_lds16(rs, dst + (w * C::IPW + u) * 1024, lo.dma[u]);
-    };
-    const float c2 = scale * kLog2e;
-
-    // One 64-key tile as two 32-key halves kt: S^T and dP^T (32x32x16), dS^T,
-    // its exchange to the 16x16 B-operand layout, and the dQ product of that
-    // half (16x16x32); only one half's score accumulators are live at a time.
-    auto step = [&](int t, const char* kt_lds, const char* vt_lds, auto masked)
-        __attribute__((always_inline)) {
-      int lim = 2 * C::ST;
-      if constexpr (decltype(masked)::value) {   // keys past N in a short last block
-        const int j = cols[p0 + t / C::SUBS];
-        lim = N - (j * BLOCK + (t % C::SUBS) * C::ST);
+        for (int e = 0; e < 8; ++e) part[ks] += (float)o[e] * (float)doop[ks][e];
       }
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        f32x16 s = f32x16{}, dp = f32x16{};
+      for (int m = C::KS / 2; m >= 1; m >>= 1)
 #pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) {
-          const int off = lo.row[ks] + kt * 32 * C::ROWB;
-          s = mfma32(*reinterpret_cast<const bf16x8*>(kt_lds + off), qop[ks], s);
-          dp = mfma32(*reinterpret_cast<const bf16x8*>(vt_lds + off), doop[ks], dp);
-        }
-        // dS^T as bf16 pairs: pq[0] holds elements 0-3, 8-11 (keys
-        // 32 kt + 4 g + {0..3, 16..19}), pq[1] elements 4-7, 12-15
-        u32x4 pq[2];
-#pragma unroll
-        for (int e = 0; e < 16; e += 2) {
-          float p0 = fast_exp2(__builtin_fmaf(s[e], c2, -lse2));
-          float p1 = fast_exp2(__builtin_fmaf(s[e + 1], c2, -lse2));
-          if constexpr (decltype(masked)::value) {
-            const int key = 32 * kt + 8 * (e >> 2) + 4 * g + (e & 3);
-            p0 = key >= lim ? 0.f : p0;
-            p1 = key + 1 >= lim ? 0.f : p1;
-          }
-          pq[(e >> 2) & 1][((e & 3) >> 1) + 2 * (e >> 3)] =
-              pack_bf16x2(p0 * (dp[e] + ndl), p1 * (dp[e + 1] + ndl));
-        }
-        // to the B-operand layout of two 16-query groups (as the forward
-        // does for P): register 0 serves queries c16, register 1 16 + c16
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const auto r = __builtin_amdgcn_permlane16_swap(pq[0][v], pq[1][v], false, false);
-          pq[0][v] = r[0];
-          pq[1][v] = r[1];
-        }
-        // dQ^T += K^T dS^T over this half's 32 keys
-#pragma unroll
-        for (int dt = 0; dt < DT16; ++dt) {
-          const char* kb = kt_lds + 32 * kt * C::ROWB + ktr[dt];
-          const s16x4 l4 = lds_read_tr16(kb);
-          const s16x4 h4 = lds_read_tr16(kb + 16 * C::ROWB);
-          const s16x8 k8 = {l4[0], l4[1], l4[2], l4[3], h4[0], h4[1], h4[2], h4[3]};
-          const bf16x8 av = __builtin_bit_cast(bf16x8, k8);
-          dq16[dt][0] = mfma16(av, __builtin_bit_cast(bf16x8, pq[0]), dq16[dt][0]);
-          dq16[dt][1] = mfma16(av, __builtin_bit_cast(bf16x8, pq[1]), dq16[dt][1]);
-        }
-      }
-    };
-    auto iter = [&](int t, auto par, auto masked) __attribute__((always_inline)) {
-      constexpr int P = decltype(par)::value;
-      if (t + 1 < T) {
-        load_tile(K, t + 1, P ? k_lds0 : k_lds1);
-        load_tile(V, t + 1, P ? v_lds0 : v_lds1);
-      }
-      step(t, P ? k_lds1 : k_lds0, P ? v_lds1 : v_lds0, masked);
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-    };
-
-    load_tile(K, 0, k_lds0);
-    load_tile(V, 0, v_lds0);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    const bool tail = (N % BLOCK != 0) && cols[p1 - 1] == (N + BLOCK - 1) / BLOCK - 1;
-    const int Tm = tail ? T - C::SUBS : T;
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using F = std::false_type;
-    using Tt = std::true_type;
-    int t = 0;
-    for (; t + 1 < Tm; t += 2) {
-      iter(t, I0{}, F{});
-      iter(t + 1, I1{}, F{});
-    }
-    if (t < Tm) {
-      iter(t, I0{}, F{});
-      for (++t; t < T; t += 2) {
-        iter(t, I1{}, Tt{});
-        if (t + 1 < T) iter(t + 1, I0{}, Tt{});
+        for (int ks = 0; ks < m; ++ks) part[ks] += part[ks + m];
+      lse2 = LSE[ar] * kLog2e;
+      ndl = -pair_sum(part[0]);
+      if (q < N && g == 0) {
+        aux[ar] = lse2;
+        aux[(int64_t)H * T_tok + ar] = ndl;
       }
     } else {
-      for (; t < T; t += 2) {
-        iter(t, I0{}, Tt{});
-        if (t + 1 < T) iter(t + 1, I1{}, Tt{});
+      lse2 = aux[ar];
+      ndl = aux[(int64_t)H * T_tok + ar];
+    }
+    if (T > 0) {
+      const LaneOffsets<C> lo(w, lane, tok_stride);
+      // K^T operand of the 16x16x32 dQ product for d tile dt, key step kc:
+      // lane group gq reads key rows 32 kc + base(gq) + (c16 >> 2) (slots
+      // 0..3) and the same + 16 (slots 4..7), columns 16 dt + 4 (c16 & 3) .. +3,
+      // base(gq) = 8 (gq & 1) + 4 (gq >> 1): the keys the dS exchange leaves in
+      // that lane group.
+      int ktr[DT16];
+#pragma unroll
+      for (int dt = 0; dt < DT16; ++dt) {
+        const int d = 16 * dt + 4 * (c16 & 3);
+        ktr[dt] = lds_off<C::CPR>(8 * (gq & 1) + 4 * (gq >> 1) + (c16 >> 2), d >> 3) + 2 * (d & 7);
+      }
+
+      auto load_tile = [&](const __bf16* X, int t, char* dst) __attribute__((always_inline)) {
+        const int j = cols[p0 + t / C::SUBS];
+        const int key0 = j * BLOCK + (t % C::SUBS) * C::ST;
+        const int nrec = key0 < N ? (N - key0 - 1) * (int)(tok_stride * 2) + 2 * D : 0;
+        const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(X + base_bh + (int64_t)key0 * tok_stride, nrec);
+#pragma unroll
+        for (int u = 0; u < C::IPW; ++u) buffer_load_lds16(rs, dst + (w * C::IPW + u) * 1024, lo.dma[u]);
+      };
+      const float c2 = scale * kLog2e;
+
+      // One 64-key tile as two 32-key halves kt: S^T and dP^T (32x32x16), dS^T,
+      // its exchange to the 16x16 B-operand layout, and the dQ product of that
+      // half (16x16x32); only one half's score accumulators are live at a time.
+      auto step = [&](int t, const char* kt_lds, const char* vt_lds, auto masked)
+          __attribute__((always_inline)) {
+        int lim = 2 * C::ST;
+        if constexpr (decltype(masked)::value) {   // keys past N in a short last block
+          const int j = cols[p0 + t / C::SUBS];
+          lim = N - (j * BLOCK + (t % C::SUBS) * C::ST);
+        }
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+          f32x16 s = f32x16{}, dp = f32x16{};
+#pragma unroll
+          for (int ks = 0; ks < C::KS; ++ks) {
+            const int off = lo.row[ks] + kt * 32 * C::ROWB;
+            s = mfma32(*reinterpret_cast<const bf16x8*>(kt_lds + off), qop[ks], s);
+            dp = mfma32(*reinterpret_cast<const bf16x8*>(vt_lds + off), doop[ks], dp);
+          }
+          // dS^T as bf16 pairs: pq[0] holds elements 0-3, 8-11 (keys
+          // 32 kt + 4 g + {0..3, 16..19}), pq[1] elements 4-7, 12-15
+          u32x4 pq[2];
+#pragma unroll
+          for (int e = 0; e < 16; e += 2) {
+            float p0 = fast_exp2(__builtin_fmaf(s[e], c2, -lse2));
+            float p1 = fast_exp2(__builtin_fmaf(s[e + 1], c2, -lse2));
+            if constexpr (decltype(masked)::value) {
+              const int key = 32 * kt + 8 * (e >> 2) + 4 * g + (e & 3);
+              p0 = key >= lim ? 0.f : p0;
+              p1 = key + 1 >= lim ? 0.f : p1;
+            }
+            pq[(e >> 2) & 1][((e & 3) >> 1) + 2 * (e >> 3)] =
+                pack_bf16x2(p0 * (dp[e] + ndl), p1 * (dp[e + 1] + ndl));
+          }
+          // to the B-operand layout of two 16-query groups (as the forward
+          // does for P): register 0 serves queries c16, register 1 16 + c16
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const auto r = __builtin_amdgcn_permlane16_swap(pq[0][v], pq[1][v], false, false);
+            pq[0][v] = r[0];
+            pq[1][v] = r[1];
+          }
+          // dQ^T += K^T dS^T over this half's 32 keys
+#pragma unroll
+          for (int dt = 0; dt < DT16; ++dt) {
+            const char* kb = kt_lds + 32 * kt * C::ROWB + ktr[dt];
+            const s16x4 l4 = lds_read_tr16(kb);
+            const s16x4 h4 = lds_read_tr16(kb + 16 * C::ROWB);
+            const s16x8 k8 = {l4[0], l4[1], l4[2], l4[3], h4[0], h4[1], h4[2], h4[3]};
+            const bf16x8 av = __builtin_bit_cast(bf16x8, k8);
+            dq16[dt][0] = mfma16(av, __builtin_bit_cast(bf16x8, pq[0]), dq16[dt][0]);
+            dq16[dt][1] = mfma16(av, __builtin_bit_cast(bf16x8, pq[1]), dq16[dt][1]);
+          }
+        }
+      };
+      auto iter = [&](int t, auto par, auto masked) __attribute__((always_inline)) {
+        constexpr int P = decltype(par)::value;
+        if (t + 1 < T) {
+          load_tile(K, t + 1, P ? k_lds0 : k_lds1);
+          load_tile(V, t + 1, P ? v_lds0 : v_lds1);
+        }
+        step(t, P ? k_lds1 : k_lds0, P ? v_lds1 : v_lds0, masked);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+      };
+
+      load_tile(K, 0, k_lds0);
+      load_tile(V, 0, v_lds0);
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      const bool tail = (N % BLOCK != 0) && cols[p1 - 1] == (N + BLOCK - 1) / BLOCK - 1;
+      const int Tm = tail ? T - C::SUBS : T;
+      using I0 = std::integral_constant<int, 0>;
+      using I1 = std::integral_constant<int, 1>;
+      using F = std::false_type;
+      using Tt = std::true_type;
+      int t = 0;
+      for (; t + 1 < Tm; t += 2) {
+        iter(t, I0{}, F{});
+        iter(t + 1, I1{}, F{});
+      }
+      if (t < Tm) {
+        iter(t, I0{}, F{});
+        for (++t; t < T; t += 2) {
+          iter(t, I1{}, Tt{});
+          if (t + 1 < T) iter(t + 1, I0{}, Tt{});
+        }
+      } else {
+        for (; t < T; t += 2) {
+          iter(t, I0{}, Tt{});
+          if (t + 1 < T) iter(t + 1, I1{}, Tt{});
+        }
       }
     }
   }
@@ -777,7 +807,27 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
     hipLaunchKernelGGL(bwd_ds_map_kernel, grid, dim3(64), 0, s, rowptr, cols, colptr, rows, sh.nblk,
                        ds.max_pairs, ds.map, ds.row_ok);
   }
-  {
+  // The order of the recompute: at head_dim 64 dQ first, with the statistics
+  // (DELTA), two launches: forward + backward at 2 x 384 x 64 took 34.4 us
+  // with the pre-pass and takes 31.9 us without. At head_dim 128 the dQ
+  // kernel has no register left for it and the pre-pass (under 1% of the
+  // backward) stays. A dQ buffer that shares memory with Q or dO, which the
+  // dK/dV pass still reads, is written last as well.
+  const uintptr_t tensor = (uintptr_t)(sh.T * sh.H * D * 2), pdq = (uintptr_t)dq;
+  auto apart = [&](const void* x) {
+    return pdq + tensor <= (uintptr_t)x || (uintptr_t)x + tensor <= pdq;
+  };
+  const bool dq_first = D == 64 && !store && apart(q) && apart(dout);
+  if constexpr (D == 64) {
+    if (dq_first) {
+      TraceScope ts_(s, "bwd_dq", D, BLOCK);
+      hipLaunchKernelGGL((bwd_dq_kernel<D, BLOCK, true>), grid, dim3(64 * (BLOCK / 32)), 0, s,
+                         bf(q), bf(k), bf(v), bf(dout), aux, static_cast<__bf16*>(dq), sh.B, sh.N,
+                         sh.H, sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T,
+                         static_cast<const int32_t*>(nullptr), by_head, bf(o), lse);
+    }
+  }
+  if (!dq_first) {
     TraceScope ts_(s, "bwd_prep", D);
     hipLaunchKernelGGL((bwd_prep_kernel<D>), dim3((unsigned)((rows_total + 255) / 256)), dim3(256), 0,
                      s, bf(o), bf(dout), lse, aux, sh.T, sh.N, sh.H, sh.cu != nullptr);
@@ -801,13 +851,14 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
                      bf(k), static_cast<const char*>(ds.tiles), static_cast<__bf16*>(dq), sh.N, sh.H,
                      sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T, ds.map, ds.row_ok, by_head);
   }
-  {
+  if (!dq_first) {
     // every query block without row_ok (all of them without stored tiles)
     TraceScope ts_(s, "bwd_dq", D, BLOCK);
-    hipLaunchKernelGGL((bwd_dq_kernel<D, BLOCK>), grid, dim3(64 * (BLOCK / 32)), 0, s,
+    hipLaunchKernelGGL((bwd_dq_kernel<D, BLOCK, false>), grid, dim3(64 * (BLOCK / 32)), 0, s,
                      bf(q), bf(k), bf(v), bf(dout), aux, static_cast<__bf16*>(dq), sh.B, sh.N, sh.H,
                      sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T,
-                     store ? static_cast<const int32_t*>(ds.row_ok) : nullptr, by_head);
+                     store ? static_cast<const int32_t*>(ds.row_ok) : nullptr, by_head,
+                     static_cast<const __bf16*>(nullptr), static_cast<const float*>(nullptr));
   }
   return hipGetLastError();
 }
