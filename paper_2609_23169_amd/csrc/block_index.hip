@@ -4,15 +4,17 @@
 // Row lists (S_i, ascending j) feed the forward and the dQ pass; column lists
 // (query blocks selecting key block j, ascending i) feed the dK/dV pass. Both
 // are built without atomics, so the output is unique and deterministic, in
-// three launches:
-//   1. the count of every row and every column;
-//   2. an in-place scan of each count array into offsets (one workgroup per
-//      array);
-//   3. fill: the same traversals, each entry written at its list's offset
-//      plus the number of set entries before it.
-// Launches 1 and 3 each build both kinds of list: their first workgroups take
+// two launches:
+//   1. the count of every row and every column, stored as ~count in the
+//      pointer array (negative, so that it can't be taken for an offset);
+//   2. fill: each workgroup adds up the counts before its own rows or columns,
+//      replaces its own counts by offsets, and writes its lists.
+// A list array of more than kPrefixMax entries takes a scan launch in between
+// (one workgroup per array) instead of the sums in launch 2.
+// Launches 1 and 2 each build both kinds of list: their first workgroups take
 // a 64-column slab of one (b, h) each (column lists), the rest take 64 mask
-// rows each (row lists).
+// rows each (row lists). Either way a workgroup's lists are one contiguous
+// run of the output: they are put together in LDS and written coalesced.
 #include <hip/hip_runtime.h>
 
 #include "common.h"
@@ -22,12 +24,64 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
-constexpr int kRowChunks = 8;     // 64-column chunks of a row loaded before their ballots
+constexpr int kRowCols = 1024;    // columns of a row per load: 16 a lane
 constexpr int kRowsPerWave = 4;   // mask rows per wave in the row lists
+constexpr int kLists = 64;        // lists per workgroup: rows, or columns of a slab
+static_assert(kLists == kWaves * kRowsPerWave, "row lists per workgroup");
+constexpr int kPrefixPer = 16;    // counts per thread of the sums in the fill
+// At 14,472 rows and columns (24 heads, 603 blocks, density 0.1) the sums add
+// about 4 us to the fill and save a scan launch of 7.8 us. The two launches now
+// take 8.8 + 15.3 us there (three launches, with a load per mask byte and a
+// store per 64 columns: 11.3 + 7.8 + 23.7 us); both are bound by the vector
+// instructions and the latencies of one pass over 8.7 MB, not by bandwidth.
+constexpr int64_t kPrefixMax = kPrefixPer * kThreads;
+// Entries (uint16) of a workgroup's lists that LDS holds; longer runs, and
+// block indices past 65535, are written straight to the output. Such lists are
+// dense, so that their stores are nearly coalesced as they are.
+constexpr int kStage = 28 * 1024;
 
 __device__ inline uint64_t lanes_below_mask() {
   const int lane = threadIdx.x & 63;
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
+}
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// kBytes mask bytes (4 or 16) at `at`, any alignment, of a mask of `total`
+// bytes; bytes past the mask read as 0. One unguarded load (a guarded load is
+// waited for before the next one is issued); read_past then redoes the few at
+// the very end of the mask byte by byte, as all of a mask shorter than kBytes.
+// Offsets fit 32 bits (masks stay below 2^31 bytes), which keeps the addresses
+// of many loads in few registers.
+template <int kBytes, bool kTiny, typename T>
+__device__ inline T load_bytes(const uint8_t* __restrict__ mask, uint32_t at, uint32_t total) {
+  T x = {};
+  if constexpr (!kTiny) __builtin_memcpy(&x, mask + min(at, total - kBytes), kBytes);
+  return x;
+}
+template <int kBytes, bool kTiny, typename T>
+__device__ inline void read_past(T& x, const uint8_t* __restrict__ mask, uint32_t at, uint32_t total) {
+  if (!kTiny && at <= total - kBytes) return;
+  uint32_t w[kBytes / 4] = {};
+  for (uint32_t b = 0; b < kBytes; ++b)
+    if (at + b < total) w[b / 4] |= (uint32_t)mask[at + b] << (8 * (b % 4));
+  __builtin_memcpy(&x, w, kBytes);
+}
+
+// Bit 8 b + 7 set when byte b of x is nonzero.
+__device__ inline uint32_t nonzero_bytes(uint32_t x) {
+  return (((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u;
+}
+
+// Inclusive sum over the wave's lanes.
+__device__ inline int wave_scan(int x) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  return x;
 }
 
 __device__ inline uint64_t readlane64(uint64_t v, int lane) {
@@ -36,61 +90,173 @@ __device__ inline uint64_t readlane64(uint64_t v, int lane) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// Row lists: each wave takes kRowsPerWave consecutive mask rows (of B*H*Nq),
-// 64 columns per ballot.
-template <bool kFill>
-__device__ void row_lists(const uint8_t* __restrict__ mask, int64_t rows, int Nk,
-                          int32_t* __restrict__ rowptr, int32_t* __restrict__ cols, int64_t cap,
-                          int64_t wg) {
-  const int64_t r0 = (wg * kWaves + (threadIdx.x >> 6)) * kRowsPerWave;
-  if (r0 >= rows) return;   // no barrier below
-  const int lane = threadIdx.x & 63;
-  int64_t pos[kRowsPerWave];
+struct FillShared {
+  int off[kLists + 1];   // offsets of this workgroup's lists
+  int red[kWaves];
+  uint16_t stage[kStage];
+};
+
+// Offsets of the workgroup's lists l0 .. l0 + n - 1 into sh.off[0 .. n]. With
+// kScanned ptr holds offsets already. Otherwise it holds ~count for the lists
+// that no workgroup has converted yet and offsets for the others: a thread may
+// see either, each one 4-byte value. The last offset seen before l0 (ptr[0] = 0
+// is one from the start) plus the counts after it is this workgroup's base.
+// Its own lists' counts are converted by itself alone, after the reads.
+template <bool kScanned>
+__device__ __forceinline__ void list_offsets(int32_t* ptr, int64_t l0, int n, FillShared& sh) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if constexpr (kScanned) {
+    if (tid <= n) sh.off[tid] = ptr[l0 + tid];
+    __syncthreads();
+    return;
+  }
+  const int own = tid < n ? ~ptr[l0 + 1 + tid] : 0;
+  // entries 1 + 4 tid + 4096 k + (0..3), clamped to the array's start instead
+  // of guarded, so that all loads are in flight at once; 0 counts past l0
+  u32x4 v[kPrefixPer / 4];
+  if (l0 >= 4) {   // entries 0..3 exist
 #pragma unroll
-  for (int q = 0; q < kRowsPerWave; ++q) pos[q] = kFill && r0 + q < rows ? rowptr[r0 + q] : 0;
-  for (int j0 = 0; j0 < Nk; j0 += 64 * kRowChunks) {
-    // every load issued before any is tested (rows past the last and columns
-    // past Nk re-read the last ones and are masked)
-    uint32_t b[kRowsPerWave][kRowChunks];
-#pragma unroll
-    for (int q = 0; q < kRowsPerWave; ++q) {
-      const uint8_t* row = mask + min(r0 + q, rows - 1) * Nk;
-#pragma unroll
-      for (int u = 0; u < kRowChunks; ++u) b[q][u] = row[min(j0 + 64 * u + lane, Nk - 1)];
-    }
-#pragma unroll
-    for (int q = 0; q < kRowsPerWave; ++q) {
-#pragma unroll
-      for (int u = 0; u < kRowChunks; ++u) {
-        const int j = j0 + 64 * u + lane;
-        const bool set = r0 + q < rows && j < Nk && b[q][u] != 0;
-        const uint64_t bal = __ballot(set);
-        if (kFill && set) {
-          const int64_t k = pos[q] + __popcll(bal & lanes_below_mask());
-          if (k < cap) cols[k] = j;
-        }
-        pos[q] += __popcll(bal);
-      }
+    for (int k = 0; k < kPrefixPer / 4; ++k) {
+      const int x = 1 + 4 * tid + 4 * kThreads * k;
+      __builtin_memcpy(&v[k], ptr + (x + 3 <= l0 ? x : 0), sizeof(u32x4));
     }
   }
-  if (!kFill && lane == 0) {
+  uint32_t all = ~0u;   // its sign stays while only counts are seen
+  int sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPrefixPer / 4; ++k) {
+    const int x = 1 + 4 * tid + 4 * kThreads * k;
+    if (x + 3 > l0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[k][e] = x + e <= l0 ? (uint32_t)ptr[x + e] : ~0u;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      all &= v[k][e];
+      sum += (int)~v[k][e];
+    }
+  }
+  if (__syncthreads_or((int)all >= 0)) {   // some list before l0 is converted
+    int seen = 0;
+#pragma unroll
+    for (int k = 0; k < kPrefixPer; ++k)
+      if ((int)v[k / 4][k % 4] >= 0) seen = 1 + 4 * tid + 4 * kThreads * (k / 4) + k % 4;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) seen = max(seen, __shfl_xor(seen, o, 64));
+    if (lane == 0) sh.red[w] = seen;
+    __syncthreads();
+    for (int x = 0; x < kWaves; ++x) seen = max(seen, sh.red[x]);
+    sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPrefixPer; ++k) {
+      const int x = 1 + 4 * tid + 4 * kThreads * (k / 4) + k % 4;
+      const int y = (int)v[k / 4][k % 4];
+      sum += x > seen ? ~y : x == seen ? y : 0;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if (lane == 0) sh.red[w] = sum;
+  __syncthreads();
+  if (w == 0) {
+    int base = 0;
+    for (int x = 0; x < kWaves; ++x) base += sh.red[x];
+    const int incl = wave_scan(own);
+    if (lane == 0) sh.off[0] = base;
+    if (lane < n) {
+      sh.off[lane + 1] = base + incl;
+      __hip_atomic_store(ptr + l0 + 1 + lane, base + incl, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  __syncthreads();
+}
+
+// The staged run of n entries from offset `base` of the output.
+__device__ inline void write_run(const FillShared& sh, int base, int n, int32_t* __restrict__ out,
+                                 int64_t cap) {
+  for (int k = threadIdx.x; k < n; k += kThreads)
+    if ((int64_t)base + k < cap) out[(int64_t)base + k] = sh.stage[k];
+}
+
+// Row lists: each wave takes kRowsPerWave consecutive mask rows (of B*H*Nq), 16
+// columns per lane: a scan of the lanes' counts places each lane's entries.
+template <bool kFill, bool kScanned, bool kTiny>
+__device__ __forceinline__ void row_lists(const uint8_t* __restrict__ mask, int64_t rows, int Nk, int32_t* rowptr,
+                          int32_t* __restrict__ cols, int64_t cap, int64_t wg, int* __restrict__ next,
+                          FillShared* sh) {
+  const int64_t w0 = wg * kLists;   // the workgroup's first row
+  const int64_t r0 = w0 + (threadIdx.x >> 6) * kRowsPerWave;
+  const int lane = threadIdx.x & 63;
+  const int own = (int)min((int64_t)kLists, rows - w0);
+  // the next entry of each of the wave's rows, in LDS (the wave's own words)
+  int* const at = next + (threadIdx.x >> 6) * kRowsPerWave;
+  int base = 0, n = 0;
+  bool staged = false;
+  if constexpr (kFill) {
+    base = sh->off[0];
+    n = sh->off[own] - base;
+    staged = n <= kStage && Nk <= 65536;
+  }
+  if (lane < kRowsPerWave)
+    at[lane] = kFill ? sh->off[min((int)(r0 - w0) + lane, own)] - base : 0;
+  const uint32_t total = (uint32_t)rows * Nk;
+#pragma unroll 1
+  for (int j0 = 0; j0 < Nk && r0 < rows; j0 += kRowCols) {
+    const int j = j0 + 16 * lane;   // this lane's 16 columns
+    u32x4 f[kRowsPerWave];
 #pragma unroll
     for (int q = 0; q < kRowsPerWave; ++q)
-      if (r0 + q < rows) rowptr[r0 + q + 1] = (int32_t)pos[q];
+      f[q] = load_bytes<16, kTiny, u32x4>(mask, (uint32_t)min(r0 + q, rows - 1) * Nk + j, total);
+    // one row at a time, the next ones' bytes moved up
+#pragma unroll 1
+    for (int q = 0; q < kRowsPerWave && r0 + q < rows; ++q) {
+      read_past<16, kTiny>(f[0], mask, (uint32_t)(r0 + q) * Nk + j, total);
+      uint32_t m = 0;   // bit e: column j + e
+#pragma unroll
+      for (int e = 0; e < 4; ++e)   // the four flags, 7 bits apart, to bits 28..31
+        m |= ((nonzero_bytes(f[0][e]) >> 7) * 0x10204080u >> 28) << (4 * e);
+      m &= j + 16 <= Nk ? 0xffffu : j < Nk ? (1u << (Nk - j)) - 1u : 0u;
+      const int incl = wave_scan(__popc(m)), p = at[q];
+      if constexpr (kFill) {
+        int k = p + incl - __popc(m);
+#pragma unroll 1
+        for (; m; m &= m - 1, ++k) {
+          const int jj = j + __builtin_ctz(m);
+          if (staged)
+            sh->stage[k] = (uint16_t)jj;
+          else if ((int64_t)base + k < cap)
+            cols[(int64_t)base + k] = jj;
+        }
+      }
+      if (lane == 63) at[q] = p + incl;
+#pragma unroll
+      for (int x = 0; x + 1 < kRowsPerWave; ++x) f[x] = f[x + 1];
+    }
+  }
+  if constexpr (kFill) {
+    __syncthreads();
+    if (staged) write_run(*sh, base, n, cols, cap);
+  } else {
+    if (r0 == 0 && lane == 0) rowptr[0] = 0;
+    if (lane < kRowsPerWave && r0 + lane < rows)
+      rowptr[r0 + lane + 1] = kScanned ? at[lane] : ~at[lane];
   }
 }
 
 // Column lists: the workgroup owns columns j0..j0+63 of one (b, h); lane c is
-// column j0 + c. Wave w walks a contiguous range of 64-row tiles; per tile
-// each lane gathers its column's 64 bits with one coalesced 64-byte load per
-// row. The waves' counts, added in wave order through LDS, place each wave's
-// rows within its columns' lists; filling then takes the columns one at a
+// column j0 + c. Wave w walks a contiguous range of 64-row tiles and gathers a
+// tile's 64 x 64 bits with 16 loads of 4 bytes per lane. The waves' counts,
+// added in wave order through LDS, place each wave's rows within its columns'
+// lists; filling then takes each lane's set bits in turn into the staged run. Lists too long for it take the columns one at a
 // time with the lanes as rows, so each column's new entries are written
 // contiguously.
-template <bool kFill>
-__device__ void col_lists(const uint8_t* __restrict__ mask, int Nq, int Nk,
-                          int32_t* __restrict__ colptr, int32_t* __restrict__ rows_out,
-                          int64_t cap, int64_t wg, int slabs, int* __restrict__ part) {
+template <bool kFill, bool kScanned, bool kTiny>
+__device__ __forceinline__ void col_lists(const uint8_t* __restrict__ mask, int Nq, int Nk, int32_t* colptr,
+                          int32_t* __restrict__ rows_out, int64_t cap, int64_t wg, int slabs,
+                          int64_t bhs, int* __restrict__ part, uint32_t* __restrict__ turn,
+                          FillShared* sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t bh = wg / slabs;
   const int j = (int)(wg % slabs) * 64 + lane;
@@ -98,77 +264,119 @@ __device__ void col_lists(const uint8_t* __restrict__ mask, int Nq, int Nk,
   const int ntiles = (Nq + 63) / 64;
   const int per = (ntiles + kWaves - 1) / kWaves;
   const int t0 = min(ntiles, w * per), t1 = min(ntiles, t0 + per);
-  const uint8_t* col = mask + bh * (int64_t)Nq * Nk + j;
+  // Bit r of lane c's result: row 64 t + r of column j0 + c. Lane l first takes
+  // rows 16 (l / 16) .. +15 of columns 4 (l % 16) .. +3 with one 4-byte load a
+  // row, collects eight rows' flags per byte, and LDS hands each column its
+  // eight bytes.
+  const uint32_t total = (uint32_t)bhs * Nq * Nk, row0 = (uint32_t)bh * Nq;
+  const int jl = (int)(wg % slabs) * 64 + 4 * (lane & 15);
+  uint32_t* const my = turn + w * 128;
   auto bits = [&](int t) __attribute__((always_inline)) {
-    const int i0 = 64 * t;
-    uint64_t m = 0;
-    if (col_ok) {
-      // 32 loads at a time, issued before any is tested (rows past Nq re-read
-      // the last row and are masked): a guard per load would wait for each
-      // one in turn
+    const int i0 = 64 * t + 16 * (lane >> 4);
+    uint32_t f[16];
 #pragma unroll
-      for (int h = 0; h < 64; h += 32) {
-        uint32_t b[32];
+    for (int u = 0; u < 16; ++u)
+      f[u] = load_bytes<4, kTiny, uint32_t>(mask, (row0 + min(i0 + u, Nq - 1)) * Nk + jl, total);
+    uint32_t lo = 0, hi = 0;
 #pragma unroll
-        for (int u = 0; u < 32; ++u) b[u] = col[(int64_t)min(i0 + h + u, Nq - 1) * Nk];
-#pragma unroll
-        for (int u = 0; u < 32; ++u)
-          if (i0 + h + u < Nq && b[u] != 0) m |= 1ull << (h + u);
-      }
+    for (int u = 0; u < 16; ++u) {
+      const uint32_t own = i0 + u < Nq ? ~0u : 0u;
+      read_past<4, kTiny>(f[u], mask, (row0 + min(i0 + u, Nq - 1)) * Nk + jl, total);
+      (u < 8 ? lo : hi) |= (nonzero_bytes(f[u]) & own) >> (7 - u % 8);
     }
-    return m;
+    // a wave's own 512 bytes: LDS operations of a wave run in order
+    my[(lane >> 4) * 32 + (lane & 15)] = lo;
+    my[(lane >> 4) * 32 + 16 + (lane & 15)] = hi;
+    __builtin_amdgcn_wave_barrier();
+    const uint8_t* const by = reinterpret_cast<const uint8_t*>(my);
+    uint64_t m = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m |= (uint64_t)by[64 * k + lane] << (8 * k);
+    __builtin_amdgcn_wave_barrier();
+    return col_ok ? m : 0ull;
   };
   // a wave with one tile (Nq <= 1024) keeps its mask for the fill
-  const uint64_t one = t1 - t0 == 1 ? bits(t0) : 0;
-  int cnt = __popcll(one);
-  if (t1 - t0 > 1)
-    for (int t = t0; t < t1; ++t) cnt += __popcll(bits(t));
+  uint64_t one = 0;
+  int cnt = 0;
+#pragma unroll 1
+  for (int t = t0; t < t1; ++t) {
+    one = bits(t);
+    cnt += __popcll(one);
+  }
   part[w * 64 + lane] = cnt;
   __syncthreads();
-  if (!kFill) {
+  if constexpr (!kFill) {
     if (w == 0 && col_ok) {
       int tot = 0;
       for (int x = 0; x < kWaves; ++x) tot += part[x * 64 + lane];
-      colptr[bh * Nk + j + 1] = tot;
+      if (wg == 0 && lane == 0) colptr[0] = 0;
+      colptr[bh * Nk + j + 1] = kScanned ? tot : ~tot;
     }
-    return;
-  }
-  // this wave's first entry of the lane's column: the column's offset plus
-  // the entries of the earlier waves' (lower) rows
-  int64_t pos = col_ok ? colptr[bh * Nk + j] : 0;
-  for (int x = 0; x < w; ++x) pos += part[x * 64 + lane];
-  for (int t = t0; t < t1; ++t) {
-    const uint64_t m = t1 - t0 == 1 ? one : bits(t);
-    // one column at a time, the lanes as the tile's rows: the column's set
-    // rows go to consecutive entries
-    for (int c = 0; c < 64; ++c) {
-      const uint64_t mc = readlane64(m, c);   // column j0 + c, rows 64 t .. +63
-      if (mc == 0) continue;
-      const int64_t pc = (int64_t)readlane64((uint64_t)pos, c);
-      if ((mc >> lane) & 1) {
-        const int64_t k = pc + __popcll(mc & lanes_below_mask());
-        if (k < cap) rows_out[k] = 64 * t + lane;
+  } else {
+    const int own = min(64, Nk - (int)(wg % slabs) * 64);
+    const int base = sh->off[0], n = sh->off[own] - base;
+    // this wave's first entry of the lane's column: the column's offset plus
+    // the entries of the earlier waves' (lower) rows
+    int pos = sh->off[min(lane, own)] - base;
+    for (int x = 0; x < w; ++x) pos += part[x * 64 + lane];
+    const bool staged = n <= kStage && Nq <= 65536;
+#pragma unroll 1
+    for (int t = t0; t < t1; ++t) {
+      if (t1 - t0 > 1) one = bits(t);
+      if (staged) {
+#pragma unroll 1
+        for (uint64_t m = one; m; m &= m - 1)
+          sh->stage[pos++] = (uint16_t)(64 * t + __builtin_ctzll(m));
+        continue;
       }
+      // one column at a time, the lanes as the tile's rows: the column's set
+      // rows go to consecutive entries
+#pragma unroll 1
+      for (int c = 0; c < 64; ++c) {
+        const uint64_t mc = readlane64(one, c);   // column j0 + c, rows 64 t .. +63
+        if (mc == 0) continue;
+        const int64_t pc = (int64_t)base + __builtin_amdgcn_readlane(pos, c);
+        if ((mc >> lane) & 1) {
+          const int64_t k = pc + __popcll(mc & lanes_below_mask());
+          if (k < cap) rows_out[k] = 64 * t + lane;
+        }
+      }
+      pos += __popcll(one);
     }
-    pos += __popcll(m);
+    __syncthreads();
+    if (staged) write_run(*sh, base, n, rows_out, cap);
   }
 }
 
-// Launch 1 (counts) and 3 (fill): workgroups [0, col_wgs) build column lists,
-// the rest row lists.
-template <bool kFill>
-__global__ __launch_bounds__(kThreads) void index_pass(const uint8_t* __restrict__ mask, int64_t rows,
+// Counts and fill: workgroups [0, col_wgs) build column lists, the rest row
+// lists. kScanned: counts and offsets are plain, with the scan in between.
+// Two workgroups on a CU (8 waves a SIMD, 64 registers): the 466 workgroups of
+// the 2K lists run in one round.
+template <bool kFill, bool kScanned, bool kTiny>
+__global__ __launch_bounds__(kThreads, 8) void index_pass(const uint8_t* __restrict__ mask, int64_t rows,
                                                        int Nq, int Nk, int slabs, int64_t col_wgs,
-                                                       int32_t* __restrict__ rowptr,
-                                                       int32_t* __restrict__ cols,
-                                                       int32_t* __restrict__ colptr,
+                                                       int32_t* rowptr, int32_t* __restrict__ cols,
+                                                       int32_t* colptr,
                                                        int32_t* __restrict__ rows_out, int64_t cap) {
   __shared__ int part[kThreads];
+  __shared__ uint32_t turn[kWaves * 128];
+  FillShared* sh = nullptr;
+  if constexpr (kFill) {
+    __shared__ FillShared fill;
+    sh = &fill;
+  }
   const int64_t wg = blockIdx.x;
+  if constexpr (kFill) {   // one copy of the code for both kinds of list
+    const bool col = wg < col_wgs;
+    const int64_t j0 = wg % slabs * 64, r0 = (wg - col_wgs) * kLists;
+    list_offsets<kScanned>(col ? colptr : rowptr, col ? wg / slabs * Nk + j0 : r0,
+                           (int)min((int64_t)kLists, col ? Nk - j0 : rows - r0), *sh);
+  }
   if (wg < col_wgs)
-    col_lists<kFill>(mask, Nq, Nk, colptr, rows_out, cap, wg, slabs, part);
+    col_lists<kFill, kScanned, kTiny>(mask, Nq, Nk, colptr, rows_out, cap, wg, slabs, rows / Nq, part,
+                              turn, sh);
   else
-    row_lists<kFill>(mask, rows, Nk, rowptr, cols, cap, wg - col_wgs);
+    row_lists<kFill, kScanned, kTiny>(mask, rows, Nk, rowptr, cols, cap, wg - col_wgs, part, sh);
 }
 
 // In-place scan: ptr[1..n] holds counts -> ptr[0..n] holds offsets.
@@ -242,21 +450,29 @@ hipError_t launch_block_index(const uint8_t* mask, int B, int H, int Nq, int Nk,
   const int64_t col_wgs = (int64_t)slabs * B * H;
   const int64_t row_wgs = (rows + kWaves * kRowsPerWave - 1) / (kWaves * kRowsPerWave);
   const dim3 grid((unsigned)(col_wgs + row_wgs));
-  {
-    TraceScope ts_(s, "index_count");
-    hipLaunchKernelGGL(index_pass<false>, grid, dim3(kThreads), 0, s, mask, rows, Nq, Nk, slabs,
-                       col_wgs, q_rowptr, q_cols, kv_colptr, kv_rows, cap);
+  const bool scan = rows > kPrefixMax || (int64_t)B * H * Nk > kPrefixMax;
+  auto pass = [&](auto kernel, const char* name) {
+    TraceScope ts_(s, name);
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, mask, rows, Nq, Nk, slabs, col_wgs,
+                       q_rowptr, q_cols, kv_colptr, kv_rows, cap);
+  };
+  if (rows * Nk < 16) {   // shorter than one load: byte by byte
+    pass(index_pass<false, false, true>, "index_count");
+    pass(index_pass<true, false, true>, "index_fill");
+    return hipGetLastError();
   }
+  if (!scan) {
+    pass(index_pass<false, false, false>, "index_count");
+    pass(index_pass<true, false, false>, "index_fill");
+    return hipGetLastError();
+  }
+  pass(index_pass<false, true, false>, "index_count");
   {
     TraceScope ts_(s, "index_scan");
     hipLaunchKernelGGL(scan_counts, dim3(2), dim3(kScanThreads), 0, s, q_rowptr, rows, kv_colptr,
                        (int64_t)B * H * Nk);
   }
-  {
-    TraceScope ts_(s, "index_fill");
-    hipLaunchKernelGGL(index_pass<true>, grid, dim3(kThreads), 0, s, mask, rows, Nq, Nk, slabs,
-                       col_wgs, q_rowptr, q_cols, kv_colptr, kv_rows, cap);
-  }
+  pass(index_pass<true, true, false>, "index_fill");
   return hipGetLastError();
 }
 
