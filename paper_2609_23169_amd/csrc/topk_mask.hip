@@ -12,9 +12,9 @@
 //            in LDS as order-preserving integer keys (fp32 MFMA for head_dim
 //            64 / 128 and rows of at most 1024 blocks; fp32 fused
 //            multiply-adds otherwise, with fewer rows per workgroup when a
-//            row is long), then each wave takes one row at a time: a 32-step
-//            radix select (counts by ballot and scalar popcount) finds the
-//            k-th largest key, and the row of the mask keeps every larger key
+//            row is long), then each wave takes one row at a time: a search by
+//            interpolation and bisection (counts by ballot and scalar popcount)
+//            finds the k-th largest key, and the row of the mask keeps every larger key
 //            plus, of the keys equal to it, the lowest block indices up to k
 //            in total. With P prefix blocks (always-kept text tokens), the
 //            first P rows are dense, the first P columns are always kept, and
@@ -95,6 +95,18 @@ __device__ inline uint32_t order_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// The inverse of order_key.
+__device__ inline float key_value(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k);
+}
+
+// Largest value over the wave's lanes, in every lane.
+__device__ inline uint32_t wave_max(uint32_t x) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) x = max(x, (uint32_t)__shfl_xor((int)x, o, 64));
+  return x;
+}
+
 // Keys of one row: in registers (M64 > 0: at most 64 * M64 blocks) or read
 // from LDS each time (M64 == 0).
 template <int M64>
@@ -108,9 +120,18 @@ struct RowKeys {
       for (int m = 0; m < M64; ++m) k[m] = 64 * m + lane < nk ? row[64 * m + lane] : 0u;
     }
   }
+  template <typename Fn>
+  __device__ void each(Fn fn) const {
+    if constexpr (M64 > 0) {
+#pragma unroll
+      for (int m = 0; m < M64; ++m) fn(k[m]);
+    } else {
+      for (int j = lane; j < nk; j += 64) fn(lds[j]);
+    }
+  }
   // Number of keys of the row for which pred(key) holds (uniform). Slots
   // past nk hold key 0, which no predicate used here accepts (they compare
-  // a key with >= T | bit or > T), so the register path needs no guard.
+  // a key with >= t, t > 0, or > T), so the register path needs no guard.
   template <typename Pred>
   __device__ int count(Pred pred) const {
     int n = 0;
@@ -124,6 +145,48 @@ struct RowKeys {
     return n;
   }
 };
+
+// The k-th largest of the row's nonzero keys, or, when exactly k keys are at
+// least as large as some key value, that value: either way every key above T
+// is kept, and of those equal to T as many as reach k in all. lo always has at
+// least k keys >= it and hi fewer; the next candidate is where the counts put
+// it on a line between the two score values, every eighth one the middle of the
+// keys, which bounds the search. A fixed 32-step radix select spent two scalar
+// instructions per 64 keys and step, and a CU issues one a cycle for its four
+// SIMDs; about 8 steps do here (normal scores, 603 blocks, k = 60).
+template <int M64>
+__device__ __forceinline__ uint32_t kth_key(const RowKeys<M64>& rk, int n, int k) {
+  uint32_t mx = 0, mn = 0;   // mn: largest complement of a nonzero key
+  rk.each([&](uint32_t x) __attribute__((always_inline)) {
+    mx = max(mx, x);
+    mn = max(mn, x ? ~x : 0u);
+  });
+  uint32_t lo = ~wave_max(mn), hi = wave_max(mx);
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  hi = __builtin_amdgcn_readfirstlane(hi);
+  if (hi != ~0u) ++hi;   // (~0: a NaN pattern, kept below)
+  int nlo = n, nhi = 0;
+  for (int it = 1; hi - lo > 1; ++it) {
+    uint32_t t = lo + ((hi - lo) >> 1);
+    if (it % 8 != 0) {
+      const float a = key_value(lo), b = key_value(hi);
+      const float f = ((float)(nlo - k) + 0.5f) / (float)(nlo - nhi);
+      const uint32_t g = order_key(__builtin_fmaf(b - a, f, a));
+      const uint32_t gu = __builtin_amdgcn_readfirstlane(g);
+      if (gu > lo && gu < hi) t = gu;
+    }
+    const int c = rk.count([t](uint32_t x) { return x >= t; });
+    if (c == k) return t;
+    if (c > k) {
+      lo = t;
+      nlo = c;
+    } else {
+      hi = t;
+      nhi = c;
+    }
+  }
+  return lo;
+}
 
 // One wave selects rows r0, r0 + step, ... of the workgroup's score rows in
 // `keys` ([rows][nk] order keys) and writes their mask rows.
@@ -140,12 +203,7 @@ __device__ void select_rows(uint32_t* keys, uint8_t* mask_rows, int i0, int rows
     // accepts (every score maps to a key >= 1), and choose among the rest.
     for (int j = lane; j < prefix; j += 64) keys[r * nk + j] = 0u;
     const RowKeys<M64> rk(keys + r * nk, nk, lane);
-    // T = the largest key with at least k_keep keys >= T, i.e. the k-th largest.
-    uint32_t T = 0;
-    for (int bit = 31; bit >= 0; --bit) {
-      const uint32_t cand = T | (1u << bit);
-      if (rk.count([cand](uint32_t x) { return x >= cand; }) >= k_keep) T = cand;
-    }
+    const uint32_t T = kth_key<M64>(rk, nk - prefix, k_keep);
     // scores equal to the k-th are taken lowest j first, up to k_keep in all
     int quota = k_keep - rk.count([T](uint32_t x) { return x > T; });
     auto emit = [&](int m, uint32_t key) __attribute__((always_inline)) {
@@ -175,25 +233,37 @@ __device__ void select_rows(uint32_t* keys, uint8_t* mask_rows, int i0, int rows
 // in fp32, as in the generic path.
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
-template <int D>
-__global__ __launch_bounds__(kSelMfmaThreads) void select_mfma_kernel(const float* __restrict__ pq,
+// Eight waves a SIMD (64 registers, the query rows in registers and not LDS):
+// four workgroups fit a CU's LDS at 603 blocks and the 912 of 24 heads run in
+// one round. With three a CU the kernel took 80 us, with four it takes 70
+// (82 with the radix select); about 40 of them are the score products (fp32
+// matrix rate: 15) and 25 the selection.
+// M64: 64-key registers of a row, at least nk / 64. With by_head (heads a
+// multiple of 8) a head's workgroups run on one XCD, whose L2 then holds that
+// head's pooled keys instead of every active head's.
+template <int D, int M64>
+__global__ __launch_bounds__(kSelMfmaThreads, 8) void select_mfma_kernel(const float* __restrict__ pq,
                                                                   const float* __restrict__ pk,
                                                                   uint8_t* __restrict__ mask,
                                                                   int nq, int nk, int k_keep,
-                                                                  int prefix) {
+                                                                  int prefix, bool by_head) {
   constexpr int QR = 16;
-  __shared__ __attribute__((aligned(16))) float sq[QR * D];
   extern __shared__ uint32_t keys[];   // [QR][nk]
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int groups = (nq + QR - 1) / QR;
-  const int64_t bh = blockIdx.x / groups;
-  const int i0 = (int)(blockIdx.x % groups) * QR;
+  // workgroups go round-robin to the 8 XCDs
+  const unsigned wg = by_head ? blockIdx.x >> 3 : blockIdx.x;
+  const int64_t bh = by_head ? (int64_t)(wg / groups) * 8 + (blockIdx.x & 7) : wg / groups;
+  const int i0 = (int)(wg % groups) * QR;
   const int rows = min(QR, nq - i0);
-  for (int x = tid; x < QR * D; x += kSelMfmaThreads)
-    sq[x] = x / D < rows ? pq[(bh * nq + i0) * D + x] : 0.f;
-  __syncthreads();
-
   const int l16 = lane & 15, g = lane >> 4;
+  // query row l16 of the group (a repeat past the last, never selected from)
+  float4 qv[D / 16];
+  {
+    const float* qrow = pq + (bh * nq + i0 + min(l16, rows - 1)) * (int64_t)D + 4 * g;
+#pragma unroll
+    for (int q = 0; q < D / 16; ++q) qv[q] = *reinterpret_cast<const float4*>(qrow + 16 * q);
+  }
   const float* const pkh = pk + bh * nk * (int64_t)D;
   for (int j0 = 16 * w; j0 < nk; j0 += 16 * (kSelMfmaThreads / 64)) {
     const int j = j0 + l16;
@@ -202,11 +272,10 @@ __global__ __launch_bounds__(kSelMfmaThreads) void select_mfma_kernel(const floa
 #pragma unroll
     for (int q = 0; q < D / 16; ++q) {
       const float4 kv = *reinterpret_cast<const float4*>(krow + 16 * q + 4 * g);
-      const float4 qv = *reinterpret_cast<const float4*>(sq + l16 * D + 16 * q + 4 * g);
-      c = __builtin_amdgcn_mfma_f32_16x16x4f32(qv.x, kv.x, c, 0, 0, 0);
-      c = __builtin_amdgcn_mfma_f32_16x16x4f32(qv.y, kv.y, c, 0, 0, 0);
-      c = __builtin_amdgcn_mfma_f32_16x16x4f32(qv.z, kv.z, c, 0, 0, 0);
-      c = __builtin_amdgcn_mfma_f32_16x16x4f32(qv.w, kv.w, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[q].x, kv.x, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[q].y, kv.y, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[q].z, kv.z, c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_16x16x4f32(qv[q].w, kv.w, c, 0, 0, 0);
     }
     // c[e] = S_c[i0 + 4 g + e, j]
     if (j < nk) {
@@ -215,7 +284,7 @@ __global__ __launch_bounds__(kSelMfmaThreads) void select_mfma_kernel(const floa
     }
   }
   __syncthreads();
-  select_rows<16>(keys, mask + (bh * nq + i0) * (int64_t)nk, i0, rows, w, kSelMfmaThreads / 64, nk,
+  select_rows<M64>(keys, mask + (bh * nq + i0) * (int64_t)nk, i0, rows, w, kSelMfmaThreads / 64, nk,
                   k_keep, prefix, lane);
 }
 
@@ -280,12 +349,19 @@ template <int D>
 hipError_t launch_select_mfma(const float* pq, const float* pk, uint8_t* mask, int B, int H,
                               int nq, int k_keep, int prefix, hipStream_t s) {
   const int groups = (nq + 15) / 16;
-  {
-    TraceScope ts_(s, "topk_select_mfma", D);
-    hipLaunchKernelGGL((select_mfma_kernel<D>), dim3((unsigned)((int64_t)B * H * groups)),
-                     dim3(kSelMfmaThreads), (size_t)16 * nq * sizeof(uint32_t), s, pq, pk, mask, nq,
-                     nq, k_keep, prefix);
-  }
+  const bool by_head = (int64_t)B * H % 8 == 0;
+  TraceScope ts_(s, "topk_select_mfma", D);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((int64_t)B * H * groups)), dim3(kSelMfmaThreads),
+                       (size_t)16 * nq * sizeof(uint32_t), s, pq, pk, mask, nq, nq, k_keep, prefix,
+                       by_head);
+  };
+  if (nq <= 256)
+    go(select_mfma_kernel<D, 4>);
+  else if (nq <= 640)
+    go(select_mfma_kernel<D, 10>);
+  else
+    go(select_mfma_kernel<D, 16>);
   return hipGetLastError();
 }
 
