@@ -30,6 +30,44 @@ __device__ inline f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// Inline assembly of device code; the host pass, whose register constraints
+// differ, sees nothing.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define UT_DEV_ASM(...) asm volatile(__VA_ARGS__)
+#else
+#define UT_DEV_ASM(...) ((void)0)
+#endif
+
+// mfma16 on an accumulator in AGPRs (c += a b). The compiler allots AGPRs to
+// such values for good, where with the builtin it moves them to VGPRs and
+// back. It does not see the instruction, so the caller keeps its hazards: two
+// wait states between a vector instruction that writes a or b and the first
+// use (wait_first puts them in), and acc_settle before c is read otherwise.
+template <bool wait_first>
+__device__ inline void acc_mfma16(f32x4& c, bf16x8 a, u32x4 b) {
+  if constexpr (wait_first)
+    UT_DEV_ASM("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  else
+    UT_DEV_ASM("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+// c = 0 as the product of zeros (z = 0): one write of the whole register group.
+__device__ inline void acc_zero16(f32x4& c, u32x4 z) {
+  UT_DEV_ASM("v_mfma_f32_16x16x32_bf16 %0, %1, %1, 0" : "=a"(c) : "v"(z));
+}
+// 32 wait states: every earlier acc_mfma16 has written its accumulator.
+__device__ inline void acc_settle() { UT_DEV_ASM("s_nop 15\n\ts_nop 15"); }
+// A use of c that stays behind acc_settle, for reads of c that follow.
+__device__ inline void acc_ready(f32x4& c) { UT_DEV_ASM("" : "+a"(c)); }
+
+// Nothing moves across pin_order; x is computed before pin_value (pure vector
+// code would otherwise sink to its use, past the matrix instructions that are
+// meant to cover it).
+__device__ inline void pin_order() { __builtin_amdgcn_sched_barrier(0); }
+template <typename T>
+__device__ inline void pin_value(T& x) {
+  UT_DEV_ASM("" : "+v"(x));
+}
+
 // Transposing LDS read: in each 16-lane group, lanes 4r..4r+3 address row r
 // (four consecutive 16-bit elements each); lane j receives element j of the
 // 16-element rows r = 0..3.
@@ -93,6 +131,19 @@ __device__ inline int swz_off(int r, int c) {
   const int sw = CPR == 16 ? (((r & 7) << 1) | ((r >> 3) & 1))
                            : ((((r >> 1) & 3) << 1) | ((r >> 3) & 1));
   return r * CPR * 16 + ((c ^ sw) << 4);
+}
+
+// LDS byte offset of logical 16-byte chunk c of row r in a tile of 256-byte
+// rows, for kernels that read the tile both ways in the 16x16x32 layouts: b128
+// reads of one chunk per 16-lane group over 16 rows, where two lanes of a
+// half-wave conflict on the same chunk position in rows of equal parity, and
+// transposing reads of rows 4g..4g+3 over two adjacent chunks, where a
+// half-wave covers rows 0..7 or 8..15. The swizzle's upper three bits differ
+// between the rows of either half and between the eight rows of one parity:
+// no conflicts (SQ_LDS_BANK_CONFLICT = 0 in the dK/dV kernel).
+__device__ inline int both_off(int r, int c) {
+  const int sw = ((r & 7) ^ ((r >> 3) & 1)) << 1;
+  return r * 256 + ((c ^ sw) << 4);
 }
 
 constexpr int kRsrcWord3 = 0x00020000;  // raw buffer descriptor, 32-bit data format

@@ -1,0 +1,83 @@
+"""GPU tests of the backward's dK/dV pass at head_dim 128, block 128 where its
+tiles end: samples ending inside a 16-row half, a 32-row tile and a wave's 64
+keys, lists longer than the 64 entries held in registers, packed samples, and
+dS tiles for part of the pairs. Against the float64 oracle (Eq. 8's gradients)
+within the tolerances of the other backward tests. Then the dQ pass that forms
+the row statistics at head_dim 64, with a gradient buffer that shares memory
+with an input."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_23169_amd as ut
+import workloads as W
+from parity import check_grad
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _run(case, **kw):
+    q, k, v, do = (case[n].to(DEV) for n in ("q", "k", "v", "do"))
+    idx = ut.build_block_index(torch.from_numpy(case["block_mask"]).to(DEV))
+    o, lse = ut.bsattn_fwd(q, k, v, idx, case["block"], case["scale"])
+    return ut.bsattn_bwd(q, k, v, o, do, lse, idx, case["block"], case["scale"], **kw)
+
+
+def _check(case, grads, label):
+    ref = oracle.bsattn_bwd(case["q"], case["k"], case["v"], case["do"], case["block_mask"],
+                            case["block"], case["scale"])
+    for got, want, nm in zip(grads, ref, ("dq", "dk", "dv")):
+        check_grad(got, want, f"{label} {nm}")
+
+
+# (not n = 1: a single key's dQ and dK are exactly 0, and the tolerance is
+# relative to the largest gradient)
+@pytest.mark.parametrize("n", [2, 15, 17, 32, 33, 63, 65, 127, 128, 129, 143, 161, 192, 209, 383])
+def test_short_blocks(n):
+    case = W.random_case(1000 + n, n, 2, 128, 128, 0.6, batch=2)
+    _check(case, _run(case), f"stored n {n}")
+    _check(case, _run(case, ds_pairs=0), f"recompute n {n}")
+
+
+@pytest.mark.parametrize("pairs", [None, 0, 70])
+def test_list_longer_than_its_registers(pairs):
+    """Key block 1 is selected by all 131 query blocks (three loads of its
+    list), the others by one or two."""
+    nb = 131
+    case = W.random_case(77, nb * 128 - 45, 1, 128, 128, 0.0)
+    case["block_mask"][:, :, :, 1] = 1
+    _check(case, _run(case, ds_pairs=pairs), f"pairs {pairs}")
+
+
+def test_packed_samples():
+    case = W.varlen_case(78, [1, 130, 0, 257, 95], 3, 128, 128, 0.5)
+    q, k, v, do = (case[n].to(DEV) for n in ("q", "k", "v", "do"))
+    cu = torch.from_numpy(case["cu_seqlens"]).to(DEV)
+    idx = ut.build_block_index(torch.from_numpy(case["block_mask"]).to(DEV))
+    a = (cu, case["max_seqlen"], idx, 128, case["scale"])
+    o, lse = ut.bsattn_fwd_varlen(q, k, v, *a)
+    got = ut.bsattn_bwd_varlen(q, k, v, o, do, lse, *a)
+    ref = oracle.bsattn_bwd_varlen(case["q"], case["k"], case["v"], case["do"], case["cu_seqlens"],
+                                   case["block_mask"], 128, case["scale"])
+    for x, y, nm in zip(got, ref, ("dq", "dk", "dv")):
+        check_grad(x, y, nm)
+
+
+@pytest.mark.parametrize("shared", ["q", "dout"])
+@pytest.mark.parametrize("block", [64, 128])
+def test_dq_written_last_over_an_input(block, shared):
+    """At head_dim 64 dQ normally goes first; over Q or dO it goes last."""
+    case = W.random_case(79, 300, 2, 64, block, 0.5)
+    want = _run(case, ds_pairs=0)
+    q, k, v, do = (case[n].to(DEV) for n in ("q", "k", "v", "do"))
+    idx = ut.build_block_index(torch.from_numpy(case["block_mask"]).to(DEV))
+    o, lse = ut.bsattn_fwd(q, k, v, idx, block, case["scale"])
+    ws = torch.empty(ut.ut_bsattn_bwd_workspace_size(1, 300, 2), dtype=torch.uint8, device=DEV)
+    dq = q if shared == "q" else do
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    assert ut.ut_bsattn_bwd(q, k, v, o, do, lse, dq, dk, dv, block, idx["q_rowptr"], idx["q_cols"],
+                            idx["kv_colptr"], idx["kv_rows"], case["scale"], ws) == ut.UT_OK
+    for x, y, nm in zip((dq, dk, dv), want, ("dq", "dk", "dv")):
+        assert torch.equal(x, y), nm
