@@ -2,9 +2,10 @@
 // per-view foreground mask into the ascending list of kept positions, and the
 // row gather / scatter between the full token grid and the packed sequence.
 //
-// Compaction is three small launches over 4 KiB mask tiles (count, one-workgroup
-// scan of the tile counts, fill), so any L up to 2^31 works and the result is
-// deterministic. The row copies are HBM-bound: one 64-lane wave moves one row
+// Compaction works on 4 KiB mask tiles. Masks of up to kFusedTiles tiles take one
+// launch, in which every workgroup counts what lies before its tile by itself;
+// longer ones take three (count, one-workgroup scan of the tile counts, fill),
+// so any L up to 2^31 works. The result is deterministic either way. The row copies are HBM-bound: one 64-lane wave moves one row
 // with 16-byte non-temporal loads and stores, all of a row's loads in flight
 // before its stores.
 #include <hip/hip_runtime.h>
@@ -109,6 +110,80 @@ __global__ __launch_bounds__(kThreads) void compact_fill(const uint8_t* __restri
   }
 }
 
+// One launch: the workgroup of tile t counts the mask before the tile (16 bytes
+// a thread and 16 KiB a step, eight steps' loads in flight), then its first 256
+// threads fill the tile. At 52 tiles (212,992 tokens) that is 260 KiB of reads
+// from L2 per workgroup at most; the three launches it replaces took 4.7 + 4.8 +
+// 5.7 us, nearly all of it launch and latency, and this one takes 8.6 us. The
+// reads grow with the square of the tiles: at kFusedTiles they are 2 MiB in all
+// and the longest workgroup's four steps of loads still cost less than a launch.
+constexpr int64_t kFusedTiles = 128;
+constexpr int kFusedThreads = 1024, kFusedBatch = 8;
+
+__global__ __launch_bounds__(kFusedThreads) void compact_fused(
+    const uint8_t* __restrict__ mask, int64_t L, int64_t capacity, int32_t* __restrict__ kept_idx,
+    int32_t* __restrict__ inv_idx, int32_t* __restrict__ n_kept) {
+  __shared__ int before_w[kFusedThreads / 64], tile_w[kThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int64_t tile = (int64_t)blockIdx.x * kCompactTile;   // whole tiles lie before it
+  const int64_t base = tile + tid * kBytesPerThread;
+  const uint32_t bits = tid < kThreads ? load_flags(mask, L, base) : 0u;
+  int before = 0;
+  constexpr int64_t kStep = kFusedThreads * kBytesPerThread;
+  if ((reinterpret_cast<uintptr_t>(mask) & 15) == 0) {
+    for (int64_t p0 = tid * kBytesPerThread; p0 < tile; p0 += kFusedBatch * kStep) {
+      uint4 v[kFusedBatch];   // (past the tile's start: clamped, not counted)
+#pragma unroll
+      for (int u = 0; u < kFusedBatch; ++u)
+        v[u] = *reinterpret_cast<const uint4*>(mask + min(p0 + u * kStep, tile - 16));
+#pragma unroll
+      for (int u = 0; u < kFusedBatch; ++u) {
+        const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+        int n = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          n += __popc((((x[q] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x[q]) & 0x80808080u);
+        before += p0 + u * kStep < tile ? n : 0;
+      }
+    }
+  } else {
+    for (int64_t p = tid * kBytesPerThread; p < tile; p += kStep)
+      before += __popc(load_flags(mask, L, p));
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+  const int inc = wave_inclusive_scan(__popc(bits));
+  if (lane == 63) {
+    before_w[w] = before;
+    if (tid < kThreads) tile_w[w] = inc;
+  }
+  __syncthreads();
+  int k = inc - __popc(bits), total = 0;
+#pragma unroll
+  for (int x = 0; x < kFusedThreads / 64; ++x) {
+    k += before_w[x];
+    total += before_w[x];
+  }
+#pragma unroll
+  for (int x = 0; x < kThreads / 64; ++x) {
+    k += x < w ? tile_w[x] : 0;
+    total += tile_w[x];
+  }
+  if (tid == 0 && blockIdx.x == gridDim.x - 1) *n_kept = total;
+  if (tid >= kThreads) return;
+  for (int e = 0; e < 16; ++e) {
+    const int64_t p = base + e;
+    if (p >= L) break;
+    if (bits & (1u << e)) {
+      if (k < capacity) kept_idx[k] = (int32_t)p;
+      if (inv_idx) inv_idx[p] = k;
+      ++k;
+    } else if (inv_idx) {
+      inv_idx[p] = -1;
+    }
+  }
+}
+
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRowsPerBlock = kThreads / 64;  // one wave per row
@@ -162,6 +237,12 @@ hipError_t launch_compact(const uint8_t* mask, int64_t L, int64_t capacity, int3
                           int32_t* inv_idx, int32_t* n_kept, int32_t* tile_scratch,
                           hipStream_t s) {
   const int64_t nt = compact_tiles(L);
+  if (nt <= kFusedTiles) {
+    TraceScope ts_(s, "compact_fused");
+    hipLaunchKernelGGL(compact_fused, dim3((unsigned)nt), dim3(kFusedThreads), 0, s, mask, L, capacity,
+                       kept_idx, inv_idx, n_kept);
+    return hipGetLastError();
+  }
   {
     TraceScope ts_(s, "compact_count");
     hipLaunchKernelGGL(compact_count, dim3((unsigned)nt), dim3(kThreads), 0, s, mask, L, tile_scratch);
