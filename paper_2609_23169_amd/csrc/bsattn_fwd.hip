@@ -63,8 +63,13 @@ struct FwdCfg {
   static_assert(TILEB % (1024 * NW) == 0, "tile must split evenly over the waves");
 };
 
+// Waves per SIMD: three at head_dim 64, block 128 (168 registers; 24 x 22,879
+// x 64, density 0.2: 778 -> 715 us). At block 64 a workgroup's LDS allows no
+// third wave (844 us, and 910 with the fewer registers), and at head_dim 128
+// three waves cost the registers that the operands need.
 template <int D, int BLOCK>
-__global__ __launch_bounds__(64 * (BLOCK / 32), (BLOCK == 128 || D == 64) ? 2 : 1) void bsattn_fwd_kernel(
+__global__ __launch_bounds__(64 * (BLOCK / 32), D == 64 && BLOCK == 128 ? 3
+                                                : (BLOCK == 128 || D == 64) ? 2 : 1) void bsattn_fwd_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     __bf16* __restrict__ O, float* __restrict__ LSE, int B, int N_all, int H, int nblk, float scale,
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ cols,

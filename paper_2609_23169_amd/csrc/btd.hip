@@ -112,12 +112,12 @@ __global__ __launch_bounds__(kThreads) void compact_fill(const uint8_t* __restri
 
 // One launch: the workgroup of tile t counts the mask before the tile (16 bytes
 // a thread and 16 KiB a step, eight steps' loads in flight), then its first 256
-// threads fill the tile. At 52 tiles (212,992 tokens) that is 260 KiB of reads
-// from L2 per workgroup at most; the three launches it replaces took 4.7 + 4.8 +
-// 5.7 us, nearly all of it launch and latency, and this one takes 8.6 us. The
-// reads grow with the square of the tiles: at kFusedTiles they are 2 MiB in all
-// and the longest workgroup's four steps of loads still cost less than a launch.
-constexpr int64_t kFusedTiles = 128;
+// threads fill the tile. The three launches it replaces took 4.7 + 4.8 + 5.7 us
+// at 52 tiles (212,992 tokens), nearly all of it launch and latency; this one
+// takes 8.6 us. Its reads grow with the square of the tiles: a call with the
+// count's readback took 40.5 us with three launches and 38.4 with one at 52
+// tiles, and 41.5 and 41.8 at 123, so the line lies in between.
+constexpr int64_t kFusedTiles = 64;
 constexpr int kFusedThreads = 1024, kFusedBatch = 8;
 
 __global__ __launch_bounds__(kFusedThreads) void compact_fused(
