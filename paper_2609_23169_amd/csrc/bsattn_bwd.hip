@@ -1,7 +1,7 @@
 // Block-sparse attention backward on gfx950: gradients of Eq. 8 (paper
 // Sec. 3.3) with the block mask held constant. No atomics, deterministic.
 // Three launches with the minimum workspace (two at head_dim 64, where dQ goes
-// first and does the pre-pass's work; five when it holds dS tiles, below):
+// first and does the pre-pass's work; four when it holds dS tiles, below):
 //
 //   prep  : per query row, LSE log2(e) and -delta = -sum_d dO[r,d] O[r,d]
 //           (fp32, two planes of the workspace);
@@ -16,8 +16,8 @@
 //   dK/dV : one workgroup per (b, h, key block j), walking the query blocks
 //           that select j (column lists) in 32-row query tiles. At head_dim
 //           128, block 128 one wave per 64 keys, described at its kernel;
-//           otherwise one wave per
-//           32 keys (K rows in registers, the key block's V rows in LDS):
+//           otherwise one wave per 32 keys (K rows in registers, the key
+//           block's V rows in LDS):
 //           S = Q K^T and dP = dO V^T (lane = key column, 32x32x16; the dP
 //           accumulator starts at -delta, so it ends as dP - delta), then
 //           dV^T += dO^T P and dK^T += Q^T dS on 16x16x32 after a
@@ -29,10 +29,10 @@
 //   dQ from stored dS (when the workspace holds the tiles): the dK/dV pass
 //           also writes each retained pair's bf16 dS tile, at the pair's
 //           column-list position, and this pass takes dQ^T += K^T dS^T from
-//           it: one product per pair instead of three. A map pass, first,
-//           gives each row-list entry its tile and flags the query blocks whose
-//           tiles all fit in the workspace; the others keep the recompute pass
-//           above.
+//           it: one product per pair instead of three. A map, built in the
+//           pre-pass's launch, gives each row-list entry its tile and flags
+//           the query blocks whose tiles all fit in the workspace; the others
+//           keep the recompute pass above.
 //
 // Without stored tiles the dQ pass recomputes S and dP instead of accumulating
 // dQ with atomics from the dK/dV pass. Tiles go from global memory straight into LDS with
@@ -50,41 +50,6 @@ namespace ut {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-
-// ---------------------------------------------------------------------------
-// prep: two planes over the statistics rows, in the layout of LSE ([B, H, N]
-// for a uniform batch, [H, T] over packed tokens otherwise):
-//   A[r] = LSE log2 e,   Dn[r] = -delta = -rowsum(dO o O)
-// ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(const __bf16* __restrict__ O,
-                                                       const __bf16* __restrict__ dO,
-                                                       const float* __restrict__ LSE,
-                                                       float* __restrict__ aux, int64_t T_tok,
-                                                       int N, int H, bool packed) {
-  constexpr int CPR = D / 8;  // lanes per (token, head) row
-  const int64_t rows = T_tok * H;
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t row = gid / CPR;  // (b, n, h) in memory order
-  const int c = (int)(gid % CPR);
-  float acc = 0.f;
-  if (row < rows) {
-    const bf16x8 o = *reinterpret_cast<const bf16x8*>(O + row * D + 8 * c);
-    const bf16x8 d = *reinterpret_cast<const bf16x8*>(dO + row * D + 8 * c);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc += (float)o[e] * (float)d[e];
-  }
-#pragma unroll
-  for (int m = CPR / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-  if (row < rows && c == 0) {
-    const int h = (int)(row % H);
-    const int64_t tok = row / H;
-    const int64_t r = packed ? (int64_t)h * T_tok + tok
-                             : ((tok / N) * H + h) * N + tok % N;
-    aux[r] = LSE[r] * kLog2e;
-    aux[rows + r] = -acc;
-  }
-}
 
 template <int D, int BLOCK, int NWAVES, int ST_ = 64>
 struct BwdCfg {
@@ -135,16 +100,31 @@ struct LaneOffsets {
 // row lies below max_pairs (its dQ then comes from the tiles). One wave per
 // query block row; entries at or past max_pairs get no map entry.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void bwd_ds_map_kernel(
-    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ cols,
-    const int32_t* __restrict__ colptr, const int32_t* __restrict__ rows_list, int nblk,
-    int64_t max_pairs, int32_t* __restrict__ map, int32_t* __restrict__ row_ok) {
-  const int64_t r = blockIdx.x;
+struct DsMapArgs {
+  const int32_t* rowptr;
+  const int32_t* cols;
+  const int32_t* colptr;
+  const int32_t* rows_list;
+  int nblk;
+  int64_t max_pairs, rows;
+  int32_t* map;
+  int32_t* row_ok;
+};
+__device__ inline void ds_map_row(const DsMapArgs& m, int64_t r) {
+  const int32_t* __restrict__ rowptr = m.rowptr;
+  const int32_t* __restrict__ cols = m.cols;
+  const int32_t* __restrict__ colptr = m.colptr;
+  const int32_t* __restrict__ rows_list = m.rows_list;
+  int32_t* __restrict__ map = m.map;
+  int32_t* __restrict__ row_ok = m.row_ok;
+  const int nblk = m.nblk, lane = threadIdx.x & 63;
+  const int64_t max_pairs = m.max_pairs;
+  if (r >= m.rows) return;
   const int i = (int)(r % nblk);
   const int64_t cbase = r - i;   // (b, h) * nblk
   const int p0 = rowptr[r], p1 = rowptr[r + 1];
   bool ok = (int64_t)p1 <= max_pairs;
-  for (int p = p0 + (int)threadIdx.x; p < p1 && (int64_t)p < max_pairs; p += 64) {
+  for (int p = p0 + lane; p < p1 && (int64_t)p < max_pairs; p += 64) {
     const int j = cols[p];
     int e = -1;
     if (j >= 0 && j < nblk) {
@@ -161,7 +141,50 @@ __global__ __launch_bounds__(64) void bwd_ds_map_kernel(
     ok = ok && e >= 0 && (int64_t)e < max_pairs;
   }
   ok = __all(ok);
-  if (threadIdx.x == 0) row_ok[r] = ok ? 1 : 0;
+  if (lane == 0) row_ok[r] = ok ? 1 : 0;
+}
+
+// ---------------------------------------------------------------------------
+// prep: two planes over the statistics rows, in the layout of LSE ([B, H, N]
+// for a uniform batch, [H, T] over packed tokens otherwise):
+//   A[r] = LSE log2 e,   Dn[r] = -delta = -rowsum(dO o O)
+// With stored tiles the launch's first map_wgs workgroups do the map: a launch
+// less, 70.4 -> 64.3 us for both at 24 x 22,879 x 128 and 168 -> 160 us for
+// eight packed samples of 6,200 (the searches wait on memory beside the stream).
+// ---------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(256) void bwd_prep_kernel(const __bf16* __restrict__ O,
+                                                       const __bf16* __restrict__ dO,
+                                                       const float* __restrict__ LSE,
+                                                       float* __restrict__ aux, int64_t T_tok,
+                                                       int N, int H, bool packed,
+                                                       DsMapArgs map, unsigned map_wgs) {
+  if (blockIdx.x < map_wgs) {   // four rows of the map, one per wave
+    ds_map_row(map, (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6));
+    return;
+  }
+  constexpr int CPR = D / 8;  // lanes per (token, head) row
+  const int64_t rows = T_tok * H;
+  const int64_t gid = (int64_t)(blockIdx.x - map_wgs) * 256 + threadIdx.x;
+  const int64_t row = gid / CPR;  // (b, n, h) in memory order
+  const int c = (int)(gid % CPR);
+  float acc = 0.f;
+  if (row < rows) {
+    const bf16x8 o = *reinterpret_cast<const bf16x8*>(O + row * D + 8 * c);
+    const bf16x8 d = *reinterpret_cast<const bf16x8*>(dO + row * D + 8 * c);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc += (float)o[e] * (float)d[e];
+  }
+#pragma unroll
+  for (int m = CPR / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
+  if (row < rows && c == 0) {
+    const int h = (int)(row % H);
+    const int64_t tok = row / H;
+    const int64_t r = packed ? (int64_t)h * T_tok + tok
+                             : ((tok / N) * H + h) * N + tok % N;
+    aux[r] = LSE[r] * kLog2e;
+    aux[rows + r] = -acc;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1137,11 +1160,6 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
   const int64_t nrow = (int64_t)sh.B * sh.H * sh.nblk;
   const dim3 grid((unsigned)nrow);
   const bool store = ds.max_pairs > 0 && ds.tiles && ds.map && ds.row_ok;
-  if (store) {
-    TraceScope ts_(s, "bwd_ds_map");
-    hipLaunchKernelGGL(bwd_ds_map_kernel, grid, dim3(64), 0, s, rowptr, cols, colptr, rows, sh.nblk,
-                       ds.max_pairs, ds.map, ds.row_ok);
-  }
   // The order of the recompute: at head_dim 64 dQ first, with the statistics
   // (DELTA), two launches: forward + backward at 2 x 384 x 64 took 34.4 us
   // with the pre-pass and takes 31.9 us without. At head_dim 128 the dQ
@@ -1163,9 +1181,12 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
     }
   }
   if (!dq_first) {
-    TraceScope ts_(s, "bwd_prep", D);
-    hipLaunchKernelGGL((bwd_prep_kernel<D>), dim3((unsigned)((rows_total + 255) / 256)), dim3(256), 0,
-                     s, bf(o), bf(dout), lse, aux, sh.T, sh.N, sh.H, sh.cu != nullptr);
+    const unsigned map_wgs = store ? (unsigned)((nrow + 3) / 4) : 0u;
+    const DsMapArgs map{rowptr, cols, colptr, rows, sh.nblk, ds.max_pairs, nrow, ds.map, ds.row_ok};
+    TraceScope ts_(s, store ? "bwd_prep_map" : "bwd_prep", D);
+    hipLaunchKernelGGL((bwd_prep_kernel<D>),
+                       dim3((unsigned)((rows_total + 255) / 256) + map_wgs), dim3(256), 0, s, bf(o),
+                       bf(dout), lse, aux, sh.T, sh.N, sh.H, sh.cu != nullptr, map, map_wgs);
   }
   auto dkdv = [&](auto kernel, int threads) {
     TraceScope ts_(s, store ? "bwd_dkdv_store" : "bwd_dkdv", D, BLOCK);
