@@ -837,7 +837,13 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
 // instructions). Operands read ahead by 3 instead of 5 groups cost 1%; waiting
 // for the loads only, not the stores, did not survive the compiler's own waits.
 // At head_dim 64 or block 64 the accumulators are half as large and the kernel
-// above is not short of registers.
+// above is not short of registers. Few workgroups do not fill the chip, and then
+// twice the work in each wave is twice the time of the longest: kernel above /
+// this one 74 / 86 us with 38 workgroups, 148 / 153 with 416, 361 / 350 with 1,248
+// at density 0.3 but 102 / 106 there at 0.05 (lists of three), 2.58 / 2.54 ms
+// with 9,600 of 16. So it takes grids of kWideTiles workgroups (four rounds of
+// the 512 that fit) and more.
+constexpr int64_t kWideTiles = 2048;
 template <bool STORE>
 __global__ __launch_bounds__(128, 1) void bwd_dkdv64_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
@@ -1195,17 +1201,14 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
                        sh.scale, colptr, rows, sh.cu, sh.T, store ? ds.tiles : nullptr,
                        store ? ds.max_pairs : (int64_t)0, by_head);
   };
+  bool wide = false;
   if constexpr (D == 128 && BLOCK == 128) {
-    if (store)
-      dkdv(bwd_dkdv64_kernel<true>, 128);
-    else
-      dkdv(bwd_dkdv64_kernel<false>, 128);
-  } else {
-    if (store)
-      dkdv(bwd_dkdv_kernel<D, BLOCK, true>, 64 * (BLOCK / 32));
-    else
-      dkdv(bwd_dkdv_kernel<D, BLOCK, false>, 64 * (BLOCK / 32));
+    wide = nrow >= kWideTiles;
+    if (wide && store) dkdv(bwd_dkdv64_kernel<true>, 128);
+    if (wide && !store) dkdv(bwd_dkdv64_kernel<false>, 128);
   }
+  if (!wide && store) dkdv(bwd_dkdv_kernel<D, BLOCK, true>, 64 * (BLOCK / 32));
+  if (!wide && !store) dkdv(bwd_dkdv_kernel<D, BLOCK, false>, 64 * (BLOCK / 32));
   if (store) {
     TraceScope ts_(s, "bwd_dq_stored", D, BLOCK);
     hipLaunchKernelGGL((bwd_dq_stored_kernel<D, BLOCK>), grid, dim3(64 * (BLOCK / 32)), 0, s,

@@ -18,51 +18,74 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-def _run(case, **kw):
-    q, k, v, do = (case[n].to(DEV) for n in ("q", "k", "v", "do"))
-    idx = ut.build_block_index(torch.from_numpy(case["block_mask"]).to(DEV))
+def _run(case, copies=1, **kw):
+    """Gradients of `copies` samples that are all the case's one sample; the
+    64-key pass takes grids of 2,048 workgroups and more."""
+    q, k, v, do = (case[n].to(DEV).repeat(copies, 1, 1, 1) for n in ("q", "k", "v", "do"))
+    idx = ut.build_block_index(torch.from_numpy(case["block_mask"]).to(DEV).repeat(copies, 1, 1, 1))
     o, lse = ut.bsattn_fwd(q, k, v, idx, case["block"], case["scale"])
+    if kw.get("ds_pairs") == "half":
+        kw["ds_pairs"] = idx["nnz"] // 2
     return ut.bsattn_bwd(q, k, v, o, do, lse, idx, case["block"], case["scale"], **kw)
+
+
+def _copies(case):
+    _, h, nb, _ = case["block_mask"].shape
+    return -(-2048 // (h * nb))
 
 
 def _check(case, grads, label):
     ref = oracle.bsattn_bwd(case["q"], case["k"], case["v"], case["do"], case["block_mask"],
                             case["block"], case["scale"])
     for got, want, nm in zip(grads, ref, ("dq", "dk", "dv")):
-        check_grad(got, want, f"{label} {nm}")
+        check_grad(got[:1], want, f"{label} {nm}")
+        if nm != "dq" or "half" not in label:   # (dQ's two passes agree to rounding only)
+            assert torch.equal(got, got[:1].expand_as(got)), f"{label} {nm}: copies differ"
 
 
 # (not n = 1: a single key's dQ and dK are exactly 0, and the tolerance is
 # relative to the largest gradient)
 @pytest.mark.parametrize("n", [2, 15, 17, 32, 33, 63, 65, 127, 128, 129, 143, 161, 192, 209, 383])
 def test_short_blocks(n):
-    case = W.random_case(1000 + n, n, 2, 128, 128, 0.6, batch=2)
-    _check(case, _run(case), f"stored n {n}")
-    _check(case, _run(case, ds_pairs=0), f"recompute n {n}")
+    case = W.random_case(1000 + n, n, 2, 128, 128, 0.6)
+    copies = _copies(case)
+    _check(case, _run(case, copies), f"stored n {n}")
+    _check(case, _run(case, copies, ds_pairs=0), f"recompute n {n}")
 
 
-@pytest.mark.parametrize("pairs", [None, 0, 70])
+@pytest.mark.parametrize("pairs", [None, 0, "half"])
 def test_list_longer_than_its_registers(pairs):
     """Key block 1 is selected by all 131 query blocks (three loads of its
     list), the others by one or two."""
     nb = 131
     case = W.random_case(77, nb * 128 - 45, 1, 128, 128, 0.0)
     case["block_mask"][:, :, :, 1] = 1
-    _check(case, _run(case, ds_pairs=pairs), f"pairs {pairs}")
+    _check(case, _run(case, _copies(case), ds_pairs=pairs), f"pairs {pairs}")
+
+
+@pytest.mark.parametrize("delta", [-1, 0])
+def test_either_side_of_the_grid_size(delta):
+    """2,047 and 2,048 workgroups: the 32-key and the 64-key pass."""
+    case = W.random_case(80, 100, 1, 128, 128, 1.0)
+    _check(case, _run(case, 2048 + delta), f"{2048 + delta} workgroups")
 
 
 def test_packed_samples():
-    case = W.varlen_case(78, [1, 130, 0, 257, 95], 3, 128, 128, 0.5)
-    q, k, v, do = (case[n].to(DEV) for n in ("q", "k", "v", "do"))
-    cu = torch.from_numpy(case["cu_seqlens"]).to(DEV)
-    idx = ut.build_block_index(torch.from_numpy(case["block_mask"]).to(DEV))
+    lens, reps = [1, 130, 0, 257, 95], 48
+    case = W.varlen_case(78, lens, 3, 128, 128, 0.5)
+    q, k, v, do = (case[n].to(DEV).repeat(reps, 1, 1) for n in ("q", "k", "v", "do"))
+    cu = torch.tensor([0] + lens * reps, device=DEV).cumsum(0).to(torch.int32)
+    idx = ut.build_block_index(torch.from_numpy(case["block_mask"]).to(DEV).repeat(reps, 1, 1, 1))
+    assert len(lens) * reps * 3 * 3 >= 2048   # workgroups
     a = (cu, case["max_seqlen"], idx, 128, case["scale"])
     o, lse = ut.bsattn_fwd_varlen(q, k, v, *a)
     got = ut.bsattn_bwd_varlen(q, k, v, o, do, lse, *a)
     ref = oracle.bsattn_bwd_varlen(case["q"], case["k"], case["v"], case["do"], case["cu_seqlens"],
                                    case["block_mask"], 128, case["scale"])
     for x, y, nm in zip(got, ref, ("dq", "dk", "dv")):
-        check_grad(x, y, nm)
+        x = x.reshape(reps, sum(lens), *x.shape[1:])
+        check_grad(x[0], y, nm)
+        assert torch.equal(x, x[:1].expand_as(x)), f"{nm}: copies differ"
 
 
 @pytest.mark.parametrize("shared", ["q", "dout"])
