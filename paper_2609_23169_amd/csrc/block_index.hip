@@ -13,8 +13,9 @@
 // (one workgroup per array) instead of the sums in launch 2.
 // Launches 1 and 2 each build both kinds of list: their first workgroups take
 // a 64-column slab of one (b, h) each (column lists), the rest take 64 mask
-// rows each (row lists). Either way a workgroup's lists are one contiguous
-// run of the output: they are put together in LDS and written coalesced.
+// rows each (row lists). Lists are put together in
+// LDS and written coalesced: a row by its wave, a slab's columns, one contiguous
+// run of the output, by the workgroup.
 #include <hip/hip_runtime.h>
 
 #include "common.h"
@@ -35,8 +36,8 @@ constexpr int kPrefixPer = 16;    // counts per thread of the sums in the fill
 // store per 64 columns: 11.3 + 7.8 + 23.7 us); both are bound by the vector
 // instructions and the latencies of one pass over 8.7 MB, not by bandwidth.
 constexpr int64_t kPrefixMax = kPrefixPer * kThreads;
-// Entries (uint16) of a workgroup's lists that LDS holds; longer runs, and
-// block indices past 65535, are written straight to the output. Such lists are
+// Entries (uint16) of a slab's columns that LDS holds; longer runs, and block
+// indices past 65535, are written straight to the output. Such columns are
 // dense, so that their stores are nearly coalesced as they are.
 constexpr int kStage = 28 * 1024;
 
@@ -192,15 +193,9 @@ __device__ __forceinline__ void row_lists(const uint8_t* __restrict__ mask, int6
   const int own = (int)min((int64_t)kLists, rows - w0);
   // the next entry of each of the wave's rows, in LDS (the wave's own words)
   int* const at = next + (threadIdx.x >> 6) * kRowsPerWave;
-  int base = 0, n = 0;
-  bool staged = false;
-  if constexpr (kFill) {
-    base = sh->off[0];
-    n = sh->off[own] - base;
-    staged = n <= kStage && Nk <= 65536;
-  }
-  if (lane < kRowsPerWave)
-    at[lane] = kFill ? sh->off[min((int)(r0 - w0) + lane, own)] - base : 0;
+  uint16_t* const mine = kFill ? sh->stage + (threadIdx.x >> 6) * (kStage / kWaves) : nullptr;
+  static_assert(kStage / kWaves >= kRowCols, "one row's piece");
+  if (lane < kRowsPerWave) at[lane] = kFill ? sh->off[min((int)(r0 - w0) + lane, own)] : 0;
   const uint32_t total = (uint32_t)rows * Nk;
 #pragma unroll 1
   for (int j0 = 0; j0 < Nk && r0 < rows; j0 += kRowCols) {
@@ -220,25 +215,23 @@ __device__ __forceinline__ void row_lists(const uint8_t* __restrict__ mask, int6
       m &= j + 16 <= Nk ? 0xffffu : j < Nk ? (1u << (Nk - j)) - 1u : 0u;
       const int incl = wave_scan(__popc(m)), p = at[q];
       if constexpr (kFill) {
-        int k = p + incl - __popc(m);
+        // the row's piece in the wave's own part of the stage (LDS operations
+        // of a wave run in order), then coalesced
+        int k = incl - __popc(m);
 #pragma unroll 1
-        for (; m; m &= m - 1, ++k) {
-          const int jj = j + __builtin_ctz(m);
-          if (staged)
-            sh->stage[k] = (uint16_t)jj;
-          else if ((int64_t)base + k < cap)
-            cols[(int64_t)base + k] = jj;
-        }
+        for (; m; m &= m - 1) mine[k++] = (uint16_t)(16 * lane + __builtin_ctz(m));
+        __builtin_amdgcn_wave_barrier();
+        const int n = __builtin_amdgcn_readlane(incl, 63);
+        for (int x = lane; x < n; x += 64)
+          if ((int64_t)p + x < cap) cols[(int64_t)p + x] = j0 + mine[x];
+        __builtin_amdgcn_wave_barrier();
       }
       if (lane == 63) at[q] = p + incl;
 #pragma unroll
       for (int x = 0; x + 1 < kRowsPerWave; ++x) f[x] = f[x + 1];
     }
   }
-  if constexpr (kFill) {
-    __syncthreads();
-    if (staged) write_run(*sh, base, n, cols, cap);
-  } else {
+  if constexpr (!kFill) {
     if (r0 == 0 && lane == 0) rowptr[0] = 0;
     if (lane < kRowsPerWave && r0 + lane < rows)
       rowptr[r0 + lane + 1] = kScanned ? at[lane] : ~at[lane];
@@ -331,7 +324,7 @@ __device__ __forceinline__ void col_lists(const uint8_t* __restrict__ mask, int 
       }
       // one column at a time, the lanes as the tile's rows: the column's set
       // rows go to consecutive entries
-#pragma unroll 1
+#pragma unroll 8
       for (int c = 0; c < 64; ++c) {
         const uint64_t mc = readlane64(one, c);   // column j0 + c, rows 64 t .. +63
         if (mc == 0) continue;

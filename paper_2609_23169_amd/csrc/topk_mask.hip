@@ -233,7 +233,8 @@ __device__ void select_rows(uint32_t* keys, uint8_t* mask_rows, int i0, int rows
 // in fp32, as in the generic path.
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
-// Eight waves a SIMD (64 registers, the query rows in registers and not LDS):
+// Eight waves a SIMD up to 640 blocks (64 registers, the query rows in registers
+// and not LDS; longer rows leave room for two workgroups a CU and need more):
 // four workgroups fit a CU's LDS at 603 blocks and the 912 of 24 heads run in
 // one round. With three a CU the kernel took 80 us, with four it takes 70
 // (82 with the radix select); about 40 of them are the score products (fp32
@@ -242,7 +243,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 // multiple of 8) a head's workgroups run on one XCD, whose L2 then holds that
 // head's pooled keys instead of every active head's.
 template <int D, int M64>
-__global__ __launch_bounds__(kSelMfmaThreads, 8) void select_mfma_kernel(const float* __restrict__ pq,
+__global__ __launch_bounds__(kSelMfmaThreads, M64 > 10 ? 4 : 8) void select_mfma_kernel(const float* __restrict__ pq,
                                                                   const float* __restrict__ pk,
                                                                   uint8_t* __restrict__ mask,
                                                                   int nq, int nk, int k_keep,
