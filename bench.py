@@ -48,17 +48,17 @@ CAL_COPY_BYTES = 1 << 28      # calibration copy: 256 MiB read + 256 MiB written
 PROFILED = {
     "workload": "c2k_train", "rho": "0.1",
     "sources": {
-        "fwd": (('bsattn_fwd.hip', 'attn_util.h'), "5c79cb75d52dbd6532c51f8b608d957a550094d53c4729ea94a07d6061e285de"),
-        "bwd": (('bsattn_bwd.hip', 'attn_util.h'), "f53406920837e147b459754918010fd9958ddb0da03c46d2c24502c8992cb1cb"),
-        "btd": (('btd.hip',), "9d09820279dfbc138cc70ea771490b39ab8760643c11869db38ebddd4c222f50"),
+        "fwd": (('bsattn_fwd.hip', 'attn_util.h'), "5bbcff441148d3fa14f1c3197da865e0813d94ae047d285a669d450cd3e67de4"),
+        "bwd": (('bsattn_bwd.hip', 'attn_util.h'), "2b0de87dada004fe950c49e27856bb0c66f6a00235564bfad69d940526e8e54c"),
+        "btd": (('btd.hip',), "3693ed358fb6d91c33f658b65c20ccc9deb2b9dbfe6b9ee7cf3cdee1733fa091"),
     },
     "kernels": {
-        "bsattn_fwd<128,128>": {"read_bytes": 4.2933e+10, "write_bytes": 4.9016e+08, "clock_ghz": 1.69, "sources": "fwd"},
-        "bwd_dkdv_store<128,128>": {"read_bytes": 5.3768e+10, "write_bytes": 2.9874e+10, "clock_ghz": 1.63, "sources": "bwd"},
-        "bwd_dq_stored<128,128>": {"read_bytes": 5.1511e+10, "write_bytes": 4.7375e+08, "clock_ghz": 2.13, "sources": "bwd"},
-        "bwd_prep<128>": {"read_bytes": 1.006e+09, "write_bytes": 9.8641e+07, "clock_ghz": 2.07, "sources": "bwd"},
-        "gather_rows": {"read_bytes": 4.7588e+08, "write_bytes": 4.7349e+08, "clock_ghz": 2.45, "sources": "btd"},
-        "scatter_rows": {"read_bytes": 4.7586e+08, "write_bytes": 4.7348e+08, "clock_ghz": 2.30, "sources": "btd"},
+        "bsattn_fwd<128,128>": {"read_bytes": 4.2809e+10, "write_bytes": 4.9016e+08, "clock_ghz": 1.67, "sources": "fwd"},
+        "bwd_dkdv_store<128,128>": {"read_bytes": 5.3586e+10, "write_bytes": 2.9874e+10, "clock_ghz": 1.75, "sources": "bwd"},
+        "bwd_dq_stored<128,128>": {"read_bytes": 5.1522e+10, "write_bytes": 4.737e+08, "clock_ghz": 2.13, "sources": "bwd"},
+        "bwd_prep_map<128>": {"read_bytes": 1.0391e+09, "write_bytes": 1.0237e+08, "clock_ghz": 2.04, "sources": "bwd"},
+        "gather_rows": {"read_bytes": 4.7588e+08, "write_bytes": 4.7349e+08, "clock_ghz": 2.31, "sources": "btd"},
+        "scatter_rows": {"read_bytes": 4.7588e+08, "write_bytes": 4.7348e+08, "clock_ghz": 2.27, "sources": "btd"},
     },
 }
 
