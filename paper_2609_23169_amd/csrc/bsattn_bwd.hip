@@ -1170,13 +1170,16 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
   // (DELTA), two launches: forward + backward at 2 x 384 x 64 took 34.4 us
   // with the pre-pass and takes 31.9 us without. At head_dim 128 the dQ
   // kernel has no register left for it and the pre-pass (under 1% of the
-  // backward) stays. A dQ buffer that shares memory with Q or dO, which the
-  // dK/dV pass still reads, is written last as well.
+  // backward) stays. A dQ buffer that shares memory with an input is written
+  // last as well: the dK/dV pass still reads Q, K, V and dO, and the dQ pass's
+  // other workgroups still read O and LSE.
   const uintptr_t tensor = (uintptr_t)(sh.T * sh.H * D * 2), pdq = (uintptr_t)dq;
-  auto apart = [&](const void* x) {
-    return pdq + tensor <= (uintptr_t)x || (uintptr_t)x + tensor <= pdq;
+  auto apart = [&](const void* x, uintptr_t bytes) {
+    return pdq + tensor <= (uintptr_t)x || (uintptr_t)x + bytes <= pdq;
   };
-  const bool dq_first = D == 64 && !store && apart(q) && apart(dout);
+  const bool dq_first = D == 64 && !store && apart(q, tensor) && apart(k, tensor) &&
+                        apart(v, tensor) && apart(dout, tensor) && apart(o, tensor) &&
+                        apart(lse, (uintptr_t)(sh.T * sh.H) * sizeof(float));
   if constexpr (D == 64) {
     if (dq_first) {
       TraceScope ts_(s, "bwd_dq", D, BLOCK);

@@ -88,19 +88,29 @@ def test_packed_samples():
         assert torch.equal(x, x[:1].expand_as(x)), f"{nm}: copies differ"
 
 
-@pytest.mark.parametrize("shared", ["q", "dout"])
+@pytest.mark.parametrize("shared", ["q", "k", "v", "o", "dout", "lse"])
 @pytest.mark.parametrize("block", [64, 128])
 def test_dq_written_last_over_an_input(block, shared):
-    """At head_dim 64 dQ normally goes first; over Q or dO it goes last."""
-    case = W.random_case(79, 300, 2, 64, block, 0.5)
+    """At head_dim 64 dQ normally goes first; over an input it goes last, after
+    every other read of Q, dO, O and LSE. K and V are also read by the dQ pass
+    itself, each workgroup its own rows only under a diagonal mask."""
+    n, h = 300, 2
+    case = W.random_case(79, n, h, 64, block, 0.0 if shared in "kv" else 0.5)
     want = _run(case, ds_pairs=0)
-    q, k, v, do = (case[n].to(DEV) for n in ("q", "k", "v", "do"))
+    x = {name: case[name].to(DEV) for name in ("q", "k", "v")}
+    x["dout"] = case["do"].to(DEV)
     idx = ut.build_block_index(torch.from_numpy(case["block_mask"]).to(DEV))
-    o, lse = ut.bsattn_fwd(q, k, v, idx, block, case["scale"])
-    ws = torch.empty(ut.ut_bsattn_bwd_workspace_size(1, 300, 2), dtype=torch.uint8, device=DEV)
-    dq = q if shared == "q" else do
-    dk, dv = torch.empty_like(k), torch.empty_like(v)
-    assert ut.ut_bsattn_bwd(q, k, v, o, do, lse, dq, dk, dv, block, idx["q_rowptr"], idx["q_cols"],
-                            idx["kv_colptr"], idx["kv_rows"], case["scale"], ws) == ut.UT_OK
-    for x, y, nm in zip((dq, dk, dv), want, ("dq", "dk", "dv")):
-        assert torch.equal(x, y), nm
+    x["o"], x["lse"] = ut.bsattn_fwd(x["q"], x["k"], x["v"], idx, block, case["scale"])
+    ws = torch.empty(ut.ut_bsattn_bwd_workspace_size(1, n, h), dtype=torch.uint8, device=DEV)
+    if shared == "lse":   # LSE within the dQ buffer
+        dq = torch.empty_like(x["q"])
+        within = dq.view(torch.float32).reshape(-1)[n * h * 16:][:n * h].view(1, h, n)
+        x["lse"] = within.copy_(x["lse"])
+    else:
+        dq = x[shared]
+    dk, dv = torch.empty_like(x["k"]), torch.empty_like(x["v"])
+    assert ut.ut_bsattn_bwd(x["q"], x["k"], x["v"], x["o"], x["dout"], x["lse"], dq, dk, dv, block,
+                            idx["q_rowptr"], idx["q_cols"], idx["kv_colptr"], idx["kv_rows"],
+                            case["scale"], ws) == ut.UT_OK
+    for a, b, nm in zip((dq, dk, dv), want, ("dq", "dk", "dv")):
+        assert torch.equal(a, b), nm
