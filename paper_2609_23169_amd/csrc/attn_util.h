@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "common.h"
+
 namespace ut {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -161,15 +163,25 @@ __device__ inline void buffer_load_lds16(__amdgpu_buffer_rsrc_t rs, char* lds, i
                                            voffset, 0, 0, 0);
 }
 
-// Tile (b, h, block) = bh nblk + block of this workgroup. Plain order, or with
-// by_head (heads a multiple of 8) each head's tiles on one XCD: workgroups go
-// round-robin to the 8 XCDs, so workgroup 8 k + x is the k-th of XCD x and
-// takes tile k of the heads x, x + 8, ...
-__device__ inline int64_t tile_index(bool by_head, int nblk) {
-  const unsigned wg = blockIdx.x;
-  if (!by_head) return wg;
-  const unsigned k = wg >> 3;
-  return (int64_t)((k / nblk) * 8 + (wg & 7)) * nblk + k % nblk;
+// Tile lt = bh nblk + i of this workgroup and its list, entries p0 .. p1 - 1: in
+// plain order, or with by_head (heads a multiple of 8) each head's tiles on one
+// XCD where the group's heads are alike. Both tiles' offsets and those of the
+// heads (one lane each; as scalar loads the compiler waits for one after the
+// other) are loaded together, so that the choice adds no memory latency.
+struct Tile {
+  unsigned lt, bh;
+  int i, p0, p1;
+};
+__device__ inline Tile tile_of(const int32_t* __restrict__ ptr, bool by_head, unsigned nblk) {
+  const unsigned wg = blockIdx.x, head = wg / nblk;
+  const Tile plain = {wg, head, (int)(wg - head * nblk), ptr[wg], ptr[wg + 1]};
+  if (!by_head) return plain;
+  const unsigned first = group_tile(head, nblk), t = head_tile(wg, first, nblk);
+  const int h0 = ptr[t], h1 = ptr[t + 1];
+  const int at = ptr[first + min(threadIdx.x & 63u, 8u) * nblk];
+  const bool alike = heads_alike([at](int x) { return __builtin_amdgcn_readlane(at, x); });
+  return {alike ? t : wg, alike ? (head & ~7u) + (wg & 7) : head,
+          alike ? (int)((wg - first) >> 3) : plain.i, alike ? h0 : plain.p0, alike ? h1 : plain.p1};
 }
 
 // Where sample b's rows live. Uniform batch (cu == nullptr): tokens

@@ -213,19 +213,18 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), D == 64 && BLOCK == 128 ? 3
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  const int64_t lt = tile_index(by_head, nblk);   // tile order: see the launcher
-  if (row_ok && row_ok[lt]) return;   // dQ comes from the stored dS tiles
-  const int i = (int)(lt % nblk);
-  const int64_t bh = lt / nblk;
-  const int h = (int)(bh % H), b = (int)(bh / H);
+  const Tile tile = tile_of(rowptr, by_head, nblk);   // tile order: see the launcher
+  if (row_ok && row_ok[tile.lt]) return;   // dQ comes from the stored dS tiles
+  const int i = tile.i;
+  const int h = (int)(tile.bh % (unsigned)H), b = (int)(tile.bh / (unsigned)H);
   const int64_t tok_stride = (int64_t)H * D;
   const SampleRows sr = sample_rows(cu_seqlens, T_tok, b, h, H, N_all);
   const int N = sr.n;
   if (N <= 0 || i * BLOCK >= N) return;
   const int64_t base_bh = sr.tok0 * tok_stride + (int64_t)h * D;
   const int q = i * BLOCK + 32 * w + l32;
-  const int p0 = rowptr[lt];
-  int p1 = rowptr[lt + 1];
+  const int p0 = tile.p0;
+  int p1 = tile.p1;
   while (p1 > p0 && cols[p1 - 1] >= (N + BLOCK - 1) / BLOCK) --p1;   // past the sample
   const int T = (p1 - p0) * C::SUBS;
 
@@ -435,18 +434,17 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dq_stored_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t lt = tile_index(by_head, nblk);
-  if (!row_ok[lt]) return;   // not all stored: the recompute pass takes it
-  const int p0 = rowptr[lt], pe = rowptr[lt + 1];
-  const int i = (int)(lt % nblk);
-  const int64_t bh = lt / nblk;
-  const int h = (int)(bh % H), b = (int)(bh / H);
+  const Tile tile = tile_of(rowptr, by_head, nblk);
+  if (!row_ok[tile.lt]) return;   // not all stored: the recompute pass takes it
+  const int i = tile.i;
+  const int h = (int)(tile.bh % (unsigned)H), b = (int)(tile.bh / (unsigned)H);
   const int64_t tok_stride = (int64_t)H * D;
   const SampleRows sr = sample_rows(cu_seqlens, T_tok, b, h, H, N_all);
   const int N = sr.n;
   if (N <= 0 || i * BLOCK >= N) return;
   const int64_t base_bh = sr.tok0 * tok_stride + (int64_t)h * D;
-  int p1 = pe;
+  const int p0 = tile.p0;
+  int p1 = tile.p1;
   while (p1 > p0 && cols[p1 - 1] >= (N + BLOCK - 1) / BLOCK) --p1;   // past the sample
   const int T = (p1 - p0) * C::SUBS;
 
@@ -598,18 +596,17 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kw = w;   // 32-key group
   const int l32 = lane & 31, g = lane >> 5;
-  const int64_t lt = tile_index(by_head, nblk);   // tile order: see the launcher
-  const int j = (int)(lt % nblk);
-  const int64_t bh = lt / nblk;
-  const int h = (int)(bh % H), b = (int)(bh / H);
+  const Tile tile = tile_of(colptr, by_head, nblk);   // tile order: see the launcher
+  const int j = tile.i;
+  const int h = (int)(tile.bh % (unsigned)H), b = (int)(tile.bh / (unsigned)H);
   const int64_t tok_stride = (int64_t)H * D;
   const SampleRows sr = sample_rows(cu_seqlens, T_tok, b, h, H, N_all);
   const int N = sr.n;
   if (N <= 0 || j * BLOCK >= N) return;   // uniform over the workgroup
   const int64_t base_bh = sr.tok0 * tok_stride + (int64_t)h * D;
   const int key = j * BLOCK + 32 * kw + l32;
-  const int p0 = colptr[lt];
-  int p1 = colptr[lt + 1];
+  const int p0 = tile.p0;
+  int p1 = tile.p1;
   while (p1 > p0 && rows_list[p1 - 1] >= (N + BLOCK - 1) / BLOCK) --p1;   // past the sample
   const int T = (p1 - p0) * C::SUBS;
 
@@ -863,17 +860,16 @@ __global__ __launch_bounds__(128, 1) void bwd_dkdv64_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, gq = lane >> 4;
-  const int64_t lt = tile_index(by_head, nblk);
-  const int j = (int)(lt % nblk);
-  const int64_t bh = lt / nblk;
-  const int h = (int)(bh % H), b = (int)(bh / H);
+  const Tile tile = tile_of(colptr, by_head, nblk);
+  const int j = tile.i;
+  const int h = (int)(tile.bh % (unsigned)H), b = (int)(tile.bh / (unsigned)H);
   const int64_t tok_stride = (int64_t)H * D;
   const SampleRows sr = sample_rows(cu_seqlens, T_tok, b, h, H, N_all);
   const int N = sr.n;
   if (N <= 0 || j * BLOCK >= N) return;
   const int64_t base_bh = sr.tok0 * tok_stride + (int64_t)h * D;
-  const int p0 = colptr[lt];
-  int p1 = colptr[lt + 1];
+  const int p0 = tile.p0;
+  int p1 = tile.p1;
   while (p1 > p0 && rows_list[p1 - 1] >= (N + BLOCK - 1) / BLOCK) --p1;
   const int npair = p1 - p0, T = npair * SUBS;
 
@@ -1160,8 +1156,8 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
   // One workgroup per (b, h, block), in plain order where a head's tensors are
   // large: workgroups go round-robin to the 8 XCDs, so all XCDs work on the
   // same few heads at once (their tensors stay in the shared last-level cache)
-  // and a run of heavy blocks is spread over every XCD. Small heads go to one
-  // XCD each (heads_by_xcd).
+  // and a run of heavy blocks is spread over every XCD. Small heads of equal
+  // work go to one XCD each (heads_by_xcd, heads_alike).
   const bool by_head = heads_by_xcd(sh);
   const int64_t nrow = (int64_t)sh.B * sh.H * sh.nblk;
   const dim3 grid((unsigned)nrow);

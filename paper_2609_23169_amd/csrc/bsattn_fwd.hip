@@ -85,10 +85,9 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), D == 64 && BLOCK == 128 ? 3
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, uniform
   const int l32 = lane & 31, g = lane >> 5;
-  const int64_t lt = tile_index(by_head, nblk);   // tile order: see the launcher
-  const int i = (int)(lt % nblk);
-  const int64_t bh = lt / nblk;
-  const int h = (int)(bh % H), b = (int)(bh / H);
+  const Tile tile = tile_of(rowptr, by_head, nblk);   // tile order: see the launcher
+  const int i = tile.i;
+  const int h = (int)(tile.bh % (unsigned)H), b = (int)(tile.bh / (unsigned)H);
   const int64_t tok_stride = (int64_t)H * D;     // elements between tokens
   const SampleRows sr = sample_rows(cu_seqlens, T_tok, b, h, H, N_all);
   const int N = sr.n;                            // this sample's tokens
@@ -96,8 +95,8 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), D == 64 && BLOCK == 128 ? 3
   const int64_t base_bh = sr.tok0 * tok_stride + (int64_t)h * D;
 
   const int q = i * BLOCK + 32 * w + l32;       // this lane's query row
-  const int p0 = rowptr[lt];
-  int p1 = rowptr[lt + 1];
+  const int p0 = tile.p0;
+  int p1 = tile.p1;
   // entries past the sample's last key block (possible only with variable
   // lengths, where the block grid is sized for the longest) are ignored
   while (p1 > p0 && cols[p1 - 1] >= (N + BLOCK - 1) / BLOCK) --p1;
@@ -374,8 +373,8 @@ hipError_t launch_fwd_t(const void* q, const void* k, const void* v, void* o, fl
   // One workgroup per (b, h, block), in plain order where a head's K and V are
   // large: workgroups go round-robin to the 8 XCDs, so all XCDs work on the
   // same few heads at once (their K and V stay in the shared last-level cache)
-  // and a run of heavy blocks is spread over every XCD. Small heads go to one
-  // XCD each (heads_by_xcd).
+  // and a run of heavy blocks is spread over every XCD. Small heads of equal
+  // work go to one XCD each (heads_by_xcd, heads_alike).
   const dim3 grid((unsigned)((int64_t)sh.B * sh.H * sh.nblk));
   {
     TraceScope ts_(s, "bsattn_fwd", D, BLOCK);

@@ -63,7 +63,7 @@ struct AttnShape {
   const int32_t* cu = nullptr;   // [B + 1] sample offsets, or null for a uniform batch
   int64_t T = 0;                 // packed tokens (B N when uniform)
 };
-// Whether the attention kernels give each XCD whole heads (tile_index) or take
+// Whether the attention kernels give each XCD whole heads (tile_of) or take
 // the tiles in plain order, all XCDs on the same heads. A workgroup streams
 // two [N, D] tensors of its head (K and V, or Q and dO): with whole heads an
 // XCD's workgroups share them in its own 4 MiB of L2, in plain order every
@@ -73,10 +73,36 @@ struct AttnShape {
 // 24 x 12,801 x 128 (6.6 MB) 1.91 / 1.89, but forward at 24 x 77,586 x 128
 // (39 MB) 7.05 / 7.52 and dK/dV there 13.4 / 13.9: eight heads at once then
 // overflow the last-level cache too. The head count has to divide by 8 so
-// that every XCD gets as many heads of every sample.
+// that every XCD gets as many heads of every sample, and the eight heads that
+// run side by side have to be alike (heads_alike, below).
 constexpr int64_t kXcdHeadBytes = (int64_t)8 << 20;
 inline bool heads_by_xcd(const AttnShape& sh) {
   return sh.H % 8 == 0 && (int64_t)sh.N * sh.D * 4 <= kXcdHeadBytes;
+}
+// First tile of the group of eight heads (8 nblk workgroups in a row) that
+// workgroup wg, of head wg / nblk in plain order, belongs to.
+constexpr unsigned group_tile(unsigned head, unsigned nblk) { return (head & ~7u) * nblk; }
+// Workgroups go round-robin to the 8 XCDs, so in a group workgroup 8 k + x is
+// the k-th of XCD x: by head it takes tile k of the group's head x.
+constexpr unsigned head_tile(unsigned wg, unsigned first, unsigned nblk) {
+  return first + ((wg - first) & 7) * nblk + ((wg - first) >> 3);
+}
+// Whether the longest of the group's eight heads, by list entries (at(x): list
+// offset of head x's first tile, at(8) the group's end), is within 1/32 of their mean: by head the XCD with the
+// longest one ends last. Heads that keep equally many blocks, as Top-K
+// selection gives, are equal. Taken by head all the same, one dense head among
+// 8 (6,552 x 128, the others 3 blocks a row) took 166 us in the forward where
+// plain order takes 124, and three dense ones on one XCD among 24 took 415
+// where it takes 186; even heads gain 2 to 7%, hence the small margin.
+template <typename At>
+constexpr bool heads_alike(At at) {
+  int32_t most = 0;
+  for (int x = 0; x < 8; ++x) {
+    const int32_t n = at(x + 1) - at(x);
+    most = n > most ? n : most;
+  }
+  const int64_t total = (int64_t)at(8) - at(0);
+  return 32 * (8 * (int64_t)most - total) <= total;
 }
 hipError_t launch_bsattn_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
                              const AttnShape& sh, const int32_t* rowptr, const int32_t* cols,

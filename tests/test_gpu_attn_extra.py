@@ -208,3 +208,22 @@ def test_lse_normalises_the_allowed_scores():
             s = Q[r, h] @ K[keys, h].T * sc
             tot = np.exp(s - L[h, r]).sum()
             assert abs(tot - 1.0) <= 2e-3, (h, r, tot)
+
+
+@pytest.mark.parametrize("dense", [(), (0,), (3, 11)])
+@pytest.mark.parametrize("D,block", [(128, 128), (128, 64), (64, 128), (64, 64)])
+def test_heads_of_uneven_work(D, block, dense):
+    """Heads a multiple of 8: a group of eight heads whose lists are equally
+    long is taken one head per XCD, a group with a dense head in plain order;
+    sixteen heads hold one group of either kind or two of the latter."""
+    H, nb = 16, 5
+    case = W.random_case(35, nb * block - 9, H, D, block, 0.0)   # diagonal only
+    for h in dense:
+        case["block_mask"][:, h] = 1
+    q, k, v, do, idx, o, lse, dq, dk, dv = _run(case)
+    O, L = oracle.bsattn_fwd(case["q"], case["k"], case["v"], case["block_mask"], block, case["scale"])
+    check_out(o, lse, O, L, "uneven heads")
+    grads = oracle.bsattn_bwd(case["q"], case["k"], case["v"], case["do"], case["block_mask"], block,
+                              case["scale"])
+    for got, ref, nm in zip((dq, dk, dv), grads, ("dq", "dk", "dv")):
+        check_grad(got, ref, f"uneven heads {nm}")
