@@ -12,9 +12,9 @@
 //            in LDS as order-preserving integer keys (fp32 MFMA for head_dim
 //            64 / 128 and rows of at most 1024 blocks; fp32 fused
 //            multiply-adds otherwise, with fewer rows per workgroup when a
-//            row is long), then each wave takes one row at a time: a search by
-//            interpolation and bisection (counts by ballot and scalar popcount)
-//            finds the k-th largest key, and the row of the mask keeps every larger key
+//            row is long), then each wave takes one row at a time: a bisection
+//            (counts by ballot and scalar popcount) finds the k-th largest key,
+//            and the row of the mask keeps every larger key
 //            plus, of the keys equal to it, the lowest block indices up to k
 //            in total. With P prefix blocks (always-kept text tokens), the
 //            first P rows are dense, the first P columns are always kept, and
@@ -95,11 +95,6 @@ __device__ inline uint32_t order_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// The inverse of order_key.
-__device__ inline float key_value(uint32_t k) {
-  return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k);
-}
-
 // Largest value over the wave's lanes, in every lane.
 __device__ inline uint32_t wave_max(uint32_t x) {
 #pragma unroll
@@ -148,42 +143,32 @@ struct RowKeys {
 
 // The k-th largest of the row's nonzero keys, or, when exactly k keys are at
 // least as large as some key value, that value: either way every key above T
-// is kept, and of those equal to T as many as reach k in all. lo always has at
-// least k keys >= it and hi fewer; the next candidate is where the counts put
-// it on a line between the two score values, every eighth one the middle of the
-// keys, which bounds the search. A fixed 32-step radix select spent two scalar
-// instructions per 64 keys and step, and a CU issues one a cycle for its four
-// SIMDs; about 8 steps do here (normal scores, 603 blocks, k = 60).
+// is kept, and of those equal to T as many as reach k in all. Bisection between
+// the row's smallest and largest key: at least k keys are >= lo and fewer than k
+// are > hi, and whatever the scores are it ends within 32 counts, mostly at the
+// first value with exactly k keys above it. A radix select takes all 32, with
+// two scalar instructions per 64 keys each, of which a CU issues one a cycle for
+// its four SIMDs. Interpolating between the two scores first takes fewer counts
+// of normal scores (9 instead of 20) but longer ones, and up to 118 counts of
+// others. Pooling and selection of 24 x 603 blocks, k = 60, radix / 8 of 9
+// steps interpolated / bisection: 242 / 234 / 223 us with normal scores,
+// 242 / 276 / 223 with one score 1,000 times the others, 242 / 363 / 236 with
+// 573 equal scores.
 template <int M64>
-__device__ __forceinline__ uint32_t kth_key(const RowKeys<M64>& rk, int n, int k) {
+__device__ __forceinline__ uint32_t kth_key(const RowKeys<M64>& rk, int k) {
   uint32_t mx = 0, mn = 0;   // mn: largest complement of a nonzero key
   rk.each([&](uint32_t x) __attribute__((always_inline)) {
     mx = max(mx, x);
     mn = max(mn, x ? ~x : 0u);
   });
-  uint32_t lo = ~wave_max(mn), hi = wave_max(mx);
-  lo = __builtin_amdgcn_readfirstlane(lo);
-  hi = __builtin_amdgcn_readfirstlane(hi);
-  if (hi != ~0u) ++hi;   // (~0: a NaN pattern, kept below)
-  int nlo = n, nhi = 0;
-  for (int it = 1; hi - lo > 1; ++it) {
-    uint32_t t = lo + ((hi - lo) >> 1);
-    if (it % 8 != 0) {
-      const float a = key_value(lo), b = key_value(hi);
-      const float f = ((float)(nlo - k) + 0.5f) / (float)(nlo - nhi);
-      const uint32_t g = order_key(__builtin_fmaf(b - a, f, a));
-      const uint32_t gu = __builtin_amdgcn_readfirstlane(g);
-      if (gu > lo && gu < hi) t = gu;
-    }
+  uint32_t lo = __builtin_amdgcn_readfirstlane(~wave_max(mn));
+  uint32_t hi = __builtin_amdgcn_readfirstlane(wave_max(mx));
+  while (lo < hi) {
+    const uint32_t t = hi - ((hi - lo) >> 1);   // lo < t <= hi
     const int c = rk.count([t](uint32_t x) { return x >= t; });
     if (c == k) return t;
-    if (c > k) {
-      lo = t;
-      nlo = c;
-    } else {
-      hi = t;
-      nhi = c;
-    }
+    if (c > k) lo = t;
+    else hi = t - 1;
   }
   return lo;
 }
@@ -203,7 +188,7 @@ __device__ void select_rows(uint32_t* keys, uint8_t* mask_rows, int i0, int rows
     // accepts (every score maps to a key >= 1), and choose among the rest.
     for (int j = lane; j < prefix; j += 64) keys[r * nk + j] = 0u;
     const RowKeys<M64> rk(keys + r * nk, nk, lane);
-    const uint32_t T = kth_key<M64>(rk, nk - prefix, k_keep);
+    const uint32_t T = kth_key<M64>(rk, k_keep);
     // scores equal to the k-th are taken lowest j first, up to k_keep in all
     int quota = k_keep - rk.count([T](uint32_t x) { return x > T; });
     auto emit = [&](int m, uint32_t key) __attribute__((always_inline)) {

@@ -140,3 +140,59 @@ def test_topk_text_prefix_full_size():
     got = _run(q, k, 128, kk, 4)
     ref, sc = oracle.topk_block_mask(q, k, 128, kk, prefix_blocks=4)
     assert check_topk(got, ref, sc, topk_tolerance(q, k, 128), kk, "text prefix", prefix=4) > 0.5
+
+
+def _exact_qk(seed, nb, D, kind):
+    """Blocks of 16 equal tokens of small integers: pooled rows and scores are
+    exact in fp32 in any order of additions, so the mask is decided, ties too."""
+    rng = np.random.default_rng(seed)
+    q = rng.integers(1, 3, (nb, D)) * rng.choice([-1, 1], (nb, D))
+    k = rng.integers(-8, 9, (nb, D)).astype(np.float64)
+    if kind == "ties":        # nearly all blocks alike
+        k[nb // 20:] = k[0]
+    elif kind == "outlier":
+        k[nb // 2] *= 1024
+    elif kind == "inf":       # scores of +inf and -inf
+        k[nb // 3, 5], k[nb // 4, 7] = np.inf, -np.inf
+    t = lambda x: torch.from_numpy(np.repeat(x, 16, 0)[None, :, None]).to(torch.bfloat16)
+    return t(q), t(k)
+
+
+@pytest.mark.parametrize("kind", ["integers", "ties", "outlier", "inf"])
+@pytest.mark.parametrize("nb,D", [(256, 128), (257, 128), (640, 128), (641, 128), (896, 128), (897, 128),
+                                  (256, 64), (257, 64), (640, 64), (641, 64), (960, 64), (961, 64),
+                                  (1025, 64), (300, 96)])
+def test_topk_exact_scores_at_row_lengths(nb, D, kind):
+    """Either side of the row lengths where the selection's registers and
+    kernels change: bit-exact against the oracle, ties lowest block first."""
+    q, k = _exact_qk(nb + D, nb, D, kind)
+    for kk, prefix in ((nb // 10, 0), (nb // 2 + 1, 3)):
+        got = _run(q, k, 16, kk, prefix)
+        ref, _ = oracle.topk_block_mask(q, k, 16, kk, prefix_blocks=prefix)
+        assert np.array_equal(got, ref), (kk, prefix)
+
+
+def test_topk_time_does_not_depend_on_the_scores():
+    """The search takes at most 32 counts of a row whatever its scores are; a
+    row of ties needs them all. Interpolation alone took 2.5 times as long."""
+    n, H, D, block = 40000, 24, 64, 64
+    g = torch.Generator(device=DEV).manual_seed(3)
+    q, k = (torch.randn((1, n, H, D), generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    tied = k.clone()
+    tied[:, 31 * block:] = k[:, :1]
+
+    def ms(kk):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        best = math.inf
+        for _ in range(5):
+            ev[0].record()
+            for _ in range(20):
+                ut.topk_block_mask(q, kk, block, 62)
+            ev[1].record()
+            ev[1].synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]))
+        return best
+
+    ms(k)
+    plain, ties = ms(k), ms(tied)
+    assert ties < 1.6 * plain, (plain, ties)
