@@ -46,11 +46,13 @@ __device__ inline int block_exclusive_scan(int x, int* total) {
   return off + inc - x;
 }
 
-// The 16 mask bytes of this thread as a bit set (bit e = byte base+e nonzero).
+// The 16 mask bytes of this thread, at any alignment, as a bit set (bit e =
+// byte base+e nonzero).
 __device__ inline uint32_t load_flags(const uint8_t* mask, int64_t L, int64_t base) {
   uint32_t bits = 0;
-  if (base + 16 <= L && ((reinterpret_cast<uintptr_t>(mask + base) & 15) == 0)) {
-    const uint4 v = *reinterpret_cast<const uint4*>(mask + base);
+  if (base + 16 <= L) {
+    uint4 v;
+    __builtin_memcpy(&v, mask + base, sizeof v);
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -130,25 +132,20 @@ __global__ __launch_bounds__(kFusedThreads) void compact_fused(
   const uint32_t bits = tid < kThreads ? load_flags(mask, L, base) : 0u;
   int before = 0;
   constexpr int64_t kStep = kFusedThreads * kBytesPerThread;
-  if ((reinterpret_cast<uintptr_t>(mask) & 15) == 0) {
-    for (int64_t p0 = tid * kBytesPerThread; p0 < tile; p0 += kFusedBatch * kStep) {
-      uint4 v[kFusedBatch];   // (past the tile's start: clamped, not counted)
+  for (int64_t p0 = tid * kBytesPerThread; p0 < tile; p0 += kFusedBatch * kStep) {
+    uint4 v[kFusedBatch];   // any alignment (past the tile's start: clamped, not counted)
 #pragma unroll
-      for (int u = 0; u < kFusedBatch; ++u)
-        v[u] = *reinterpret_cast<const uint4*>(mask + min(p0 + u * kStep, tile - 16));
+    for (int u = 0; u < kFusedBatch; ++u)
+      __builtin_memcpy(&v[u], mask + min(p0 + u * kStep, tile - 16), sizeof(uint4));
 #pragma unroll
-      for (int u = 0; u < kFusedBatch; ++u) {
-        const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-        int n = 0;
+    for (int u = 0; u < kFusedBatch; ++u) {
+      const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+      int n = 0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          n += __popc((((x[q] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x[q]) & 0x80808080u);
-        before += p0 + u * kStep < tile ? n : 0;
-      }
+      for (int q = 0; q < 4; ++q)
+        n += __popc((((x[q] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x[q]) & 0x80808080u);
+      before += p0 + u * kStep < tile ? n : 0;
     }
-  } else {
-    for (int64_t p = tid * kBytesPerThread; p < tile; p += kStep)
-      before += __popc(load_flags(mask, L, p));
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);

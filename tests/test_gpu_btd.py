@@ -40,6 +40,33 @@ def test_compaction_unaligned_mask_pointer():
     assert d["n_kept"] == n_ref and np.array_equal(d["kept_idx"].cpu().numpy(), kept_ref)
 
 
+def test_compaction_time_of_an_unaligned_mask():
+    """64 tiles, the most that one launch takes: a mask that starts at an odd
+    address is counted with the same wide loads (byte by byte it took 5 times
+    as long) and gives the same lists."""
+    L = 64 * 4096
+    m = _mask(L, 0.4, 9)
+    kept_ref, _, n_ref = oracle.compact(m)
+    buf = torch.zeros(L + 16, dtype=torch.uint8, device=DEV)
+    ms = {}
+    for off in (0, 1, 6):
+        buf[off:off + L] = torch.from_numpy(m).to(DEV)
+        view = buf[off:off + L]
+        d = ut.drop_background(view)
+        assert d["n_kept"] == n_ref and np.array_equal(d["kept_idx"].cpu().numpy(), kept_ref)
+        ut.ut_trace_enable(1)
+        try:
+            for _ in range(20):
+                ut.drop_background(view)
+            torch.cuda.synchronize()
+            rows = [t for t in ut.trace_read() if t["name"].startswith("compact")]
+        finally:
+            ut.ut_trace_enable(0)
+        assert [t["name"] for t in rows] == ["compact_fused"]
+        ms[off] = rows[0]["total_ms"]
+    assert max(ms[1], ms[6]) < 2 * ms[0], ms
+
+
 @pytest.mark.parametrize("L,row_elems,p", [(777, 8, 0.4), (5000, 24, 0.6), (4096, 3072, 0.35),
                                            (33, 64, 1.0), (50, 64, 0.0),
                                            # ~180K kept rows: more than one pass of the
