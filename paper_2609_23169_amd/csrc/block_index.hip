@@ -49,24 +49,36 @@ __device__ inline uint64_t lanes_below_mask() {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // kBytes mask bytes (4 or 16) at `at`, any alignment, of a mask of `total`
-// bytes; bytes past the mask read as 0. One unguarded load (a guarded load is
-// waited for before the next one is issued); read_past then redoes the few at
-// the very end of the mask byte by byte, as all of a mask shorter than kBytes.
+// bytes; bytes past the mask read as 0. One unguarded load, clamped to the
+// mask's last kBytes (a guarded load is waited for before the next one is
+// issued); past_end then shifts what was clamped into place, for the few waves
+// that read there. A mask shorter than kBytes is read byte by byte.
 // Offsets fit 32 bits (masks stay below 2^31 bytes), which keeps the addresses
 // of many loads in few registers.
 template <int kBytes, bool kTiny, typename T>
 __device__ inline T load_bytes(const uint8_t* __restrict__ mask, uint32_t at, uint32_t total) {
   T x = {};
-  if constexpr (!kTiny) __builtin_memcpy(&x, mask + min(at, total - kBytes), kBytes);
+  if constexpr (kTiny) {
+    uint32_t w[kBytes / 4] = {};
+    for (uint32_t b = 0; b < kBytes; ++b)
+      if (at + b < total) w[b / 4] |= (uint32_t)mask[at + b] << (8 * (b % 4));
+    __builtin_memcpy(&x, w, kBytes);
+  } else {
+    __builtin_memcpy(&x, mask + min(at, total - kBytes), kBytes);
+  }
   return x;
 }
-template <int kBytes, bool kTiny, typename T>
-__device__ inline void read_past(T& x, const uint8_t* __restrict__ mask, uint32_t at, uint32_t total) {
-  if (!kTiny && at <= total - kBytes) return;
-  uint32_t w[kBytes / 4] = {};
-  for (uint32_t b = 0; b < kBytes; ++b)
-    if (at + b < total) w[b / 4] |= (uint32_t)mask[at + b] << (8 * (b % 4));
-  __builtin_memcpy(&x, w, kBytes);
+__device__ inline void past_end(uint32_t& x, uint32_t at, uint32_t total) {
+  if (at <= total - 4) return;
+  x = at < total ? x >> (8 * (at + 4 - total)) : 0u;
+}
+__device__ inline void past_end(u32x4& x, uint32_t at, uint32_t total) {
+  if (at <= total - 16) return;
+  const uint32_t gone = at < total ? at + 16 - total : 16;   // bytes before `at` in x
+  for (uint32_t b = 0; b < gone / 4; ++b) x = u32x4{x[1], x[2], x[3], 0u};
+#pragma unroll
+  for (int e = 0; e < 4; ++e)   // (the double word above the last is 0)
+    x[e] = (uint32_t)((((uint64_t)(e < 3 ? x[e + 1] : 0u) << 32) | x[e]) >> (8 * (gone % 4)));
 }
 
 // Bit 8 b + 7 set when byte b of x is nonzero.
@@ -188,12 +200,13 @@ __device__ __forceinline__ void row_lists(const uint8_t* __restrict__ mask, int6
                           int32_t* __restrict__ cols, int64_t cap, int64_t wg, int* __restrict__ next,
                           FillShared* sh) {
   const int64_t w0 = wg * kLists;   // the workgroup's first row
-  const int64_t r0 = w0 + (threadIdx.x >> 6) * kRowsPerWave;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t r0 = w0 + w * kRowsPerWave;
   const int lane = threadIdx.x & 63;
   const int own = (int)min((int64_t)kLists, rows - w0);
   // the next entry of each of the wave's rows, in LDS (the wave's own words)
-  int* const at = next + (threadIdx.x >> 6) * kRowsPerWave;
-  uint16_t* const mine = kFill ? sh->stage + (threadIdx.x >> 6) * (kStage / kWaves) : nullptr;
+  int* const at = next + w * kRowsPerWave;
+  uint16_t* const mine = kFill ? sh->stage + w * (kStage / kWaves) : nullptr;
   static_assert(kStage / kWaves >= kRowCols, "one row's piece");
   if (lane < kRowsPerWave) at[lane] = kFill ? sh->off[min((int)(r0 - w0) + lane, own)] : 0;
   const uint32_t total = (uint32_t)rows * Nk;
@@ -204,10 +217,13 @@ __device__ __forceinline__ void row_lists(const uint8_t* __restrict__ mask, int6
 #pragma unroll
     for (int q = 0; q < kRowsPerWave; ++q)
       f[q] = load_bytes<16, kTiny, u32x4>(mask, (uint32_t)min(r0 + q, rows - 1) * Nk + j, total);
+    if (!kTiny && (uint32_t)min(r0 + kRowsPerWave - 1, rows - 1) * Nk + j0 + 16 * 63 > total - 16) {
+#pragma unroll
+      for (int q = 0; q < kRowsPerWave; ++q) past_end(f[q], (uint32_t)min(r0 + q, rows - 1) * Nk + j, total);
+    }
     // one row at a time, the next ones' bytes moved up
 #pragma unroll 1
     for (int q = 0; q < kRowsPerWave && r0 + q < rows; ++q) {
-      read_past<16, kTiny>(f[0], mask, (uint32_t)(r0 + q) * Nk + j, total);
       uint32_t m = 0;   // bit e: column j + e
 #pragma unroll
       for (int e = 0; e < 4; ++e)   // the four flags, 7 bits apart, to bits 28..31
@@ -250,7 +266,7 @@ __device__ __forceinline__ void col_lists(const uint8_t* __restrict__ mask, int 
                           int32_t* __restrict__ rows_out, int64_t cap, int64_t wg, int slabs,
                           int64_t bhs, int* __restrict__ part, uint32_t* __restrict__ turn,
                           FillShared* sh) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t bh = wg / slabs;
   const int j = (int)(wg % slabs) * 64 + lane;
   const bool col_ok = j < Nk;
@@ -270,11 +286,14 @@ __device__ __forceinline__ void col_lists(const uint8_t* __restrict__ mask, int 
 #pragma unroll
     for (int u = 0; u < 16; ++u)
       f[u] = load_bytes<4, kTiny, uint32_t>(mask, (row0 + min(i0 + u, Nq - 1)) * Nk + jl, total);
+    if (!kTiny && (row0 + min(64 * t + 63, Nq - 1)) * Nk + (uint32_t)(wg % slabs) * 64 + 60 > total - 4) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) past_end(f[u], (row0 + min(i0 + u, Nq - 1)) * Nk + jl, total);
+    }
     uint32_t lo = 0, hi = 0;
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const uint32_t own = i0 + u < Nq ? ~0u : 0u;
-      read_past<4, kTiny>(f[u], mask, (row0 + min(i0 + u, Nq - 1)) * Nk + jl, total);
       (u < 8 ? lo : hi) |= (nonzero_bytes(f[u]) & own) >> (7 - u % 8);
     }
     // a wave's own 512 bytes: LDS operations of a wave run in order

@@ -38,9 +38,33 @@ def _check(bm):
     ((1, 64, 256, 9), 0.3), ((1, 64, 257, 9), 0.3),                     # rows at and past the sums
     ((1, 64, 9, 257), 0.3),                                             # columns past them
     ((1, 5, 33, 77), 0.0),
+    ((1, 24, 6, 6), 0.4), ((1, 1, 4, 4), 0.6), ((1, 1, 4, 5), 0.6),     # every slab reads past the end
+    ((1, 1, 1, 1019), 0.9), ((1, 1, 2, 1021), 0.9),                     # 1 to 15 bytes of the last load
+    ((1, 1, 3, 1030), 0.9), ((1, 1, 1, 31), 1.0),
 ])
 def test_edges(shape, density):
     _check(_mask(sum(shape), shape, density))
+
+
+def test_small_masks_take_no_longer_than_larger_ones():
+    """All of a small mask's slabs read near its end, which is clamped and
+    shifted there; byte by byte, 30 blocks took longer than 52."""
+    def us(nb):
+        bm = torch.from_numpy(_mask(nb, (1, 24, nb, nb), 0.3)).to(DEV)
+        ut.build_block_index(bm)
+        ut.ut_trace_enable(1)
+        try:
+            for _ in range(50):
+                ut.build_block_index(bm)
+            return sum(t["total_ms"] for t in ut.trace_read()) * 20
+        finally:
+            ut.ut_trace_enable(0)
+
+    us(52)
+    large = min(us(52) for _ in range(3))
+    for nb in (6, 30):
+        small = min(us(nb) for _ in range(3))
+        assert small < 1.1 * large, (nb, small, large)
 
 
 def test_capacity_below_the_entries():
