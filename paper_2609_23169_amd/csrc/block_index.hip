@@ -86,6 +86,15 @@ __device__ inline uint32_t nonzero_bytes(uint32_t x) {
   return (((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u;
 }
 
+// Between the LDS writes of a wave's lanes and the reads of others of its
+// lanes: the hardware runs a wave's LDS operations in order, the fences keep the
+// compiler from moving them across (wave_barrier alone orders no memory).
+__device__ inline void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Inclusive sum over the wave's lanes.
 __device__ inline int wave_scan(int x) {
   const int lane = threadIdx.x & 63;
@@ -209,6 +218,7 @@ __device__ __forceinline__ void row_lists(const uint8_t* __restrict__ mask, int6
   uint16_t* const mine = kFill ? sh->stage + w * (kStage / kWaves) : nullptr;
   static_assert(kStage / kWaves >= kRowCols, "one row's piece");
   if (lane < kRowsPerWave) at[lane] = kFill ? sh->off[min((int)(r0 - w0) + lane, own)] : 0;
+  wave_lds_order();
   const uint32_t total = (uint32_t)rows * Nk;
 #pragma unroll 1
   for (int j0 = 0; j0 < Nk && r0 < rows; j0 += kRowCols) {
@@ -231,18 +241,18 @@ __device__ __forceinline__ void row_lists(const uint8_t* __restrict__ mask, int6
       m &= j + 16 <= Nk ? 0xffffu : j < Nk ? (1u << (Nk - j)) - 1u : 0u;
       const int incl = wave_scan(__popc(m)), p = at[q];
       if constexpr (kFill) {
-        // the row's piece in the wave's own part of the stage (LDS operations
-        // of a wave run in order), then coalesced
+        // the row's piece in the wave's own part of the stage, then coalesced
         int k = incl - __popc(m);
 #pragma unroll 1
         for (; m; m &= m - 1) mine[k++] = (uint16_t)(16 * lane + __builtin_ctz(m));
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
         const int n = __builtin_amdgcn_readlane(incl, 63);
         for (int x = lane; x < n; x += 64)
           if ((int64_t)p + x < cap) cols[(int64_t)p + x] = j0 + mine[x];
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
       }
       if (lane == 63) at[q] = p + incl;
+      wave_lds_order();   // before the row's next piece, and the counts below
 #pragma unroll
       for (int x = 0; x + 1 < kRowsPerWave; ++x) f[x] = f[x + 1];
     }
@@ -296,15 +306,15 @@ __device__ __forceinline__ void col_lists(const uint8_t* __restrict__ mask, int 
       const uint32_t own = i0 + u < Nq ? ~0u : 0u;
       (u < 8 ? lo : hi) |= (nonzero_bytes(f[u]) & own) >> (7 - u % 8);
     }
-    // a wave's own 512 bytes: LDS operations of a wave run in order
+    // through a wave's own 512 bytes
     my[(lane >> 4) * 32 + (lane & 15)] = lo;
     my[(lane >> 4) * 32 + 16 + (lane & 15)] = hi;
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     const uint8_t* const by = reinterpret_cast<const uint8_t*>(my);
     uint64_t m = 0;
 #pragma unroll
     for (int k = 0; k < 8; ++k) m |= (uint64_t)by[64 * k + lane] << (8 * k);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     return col_ok ? m : 0ull;
   };
   // a wave with one tile (Nq <= 1024) keeps its mask for the fill
