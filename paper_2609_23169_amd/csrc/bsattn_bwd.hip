@@ -837,10 +837,21 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
 // above is not short of registers. Few workgroups do not fill the chip, and then
 // twice the work in each wave is twice the time of the longest: kernel above /
 // this one 74 / 86 us with 38 workgroups, 148 / 153 with 416, 361 / 350 with 1,248
-// at density 0.3 but 102 / 106 there at 0.05 (lists of three), 2.58 / 2.54 ms
-// with 9,600 of 16. So it takes grids of kWideTiles workgroups (four rounds of
-// the 512 that fit) and more.
-constexpr int64_t kWideTiles = 2048;
+// at density 0.3 but 102 / 106 there at 0.05 (lists of three). So it takes grids
+// of kWideTiles workgroups (four rounds of the 512 that fit) and more.
+// Nothing else runs on a SIMD while its wave starts or ends a list, which the
+// shortest lists feel: whole backward with stored tiles, 24 heads, kernel above /
+// this one at 1, 2, 3 and 5 entries a list 375 / 379, 461 / 469, 556 / 560 and
+// 759 / 748 us at 22,879 tokens, 266 / 276 at 2 and 12,000. How long lists are is
+// known here from the room for their tiles only, so below kWideList tiles a list
+// the kernel above stays; without stored tiles, or with more room than the lists
+// need, lists of one or two entries cost up to 4%. A single list longer than all
+// others together keep one of the 512 places busy is a serial chain of its own,
+// twice as long here: one dense column of 179 or 602 entries among lists of three
+// in each of 12 or 4 heads takes 1,105 / 1,247 and 3,103 / 3,600 us. (The four
+// dense rows and columns of a text prefix at 24 heads are shorter than that:
+// 28.3 / 27.7 ms at 77,060 tokens and lists of 64.)
+constexpr int64_t kWideTiles = 2048, kWideList = 3;
 template <bool STORE>
 __global__ __launch_bounds__(128, 1) void bwd_dkdv64_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
@@ -868,12 +879,225 @@ __global__ __launch_bounds__(128, 1) void bwd_dkdv64_kernel(
   const int N = sr.n;
   if (N <= 0 || j * BLOCK >= N) return;
   const int64_t base_bh = sr.tok0 * tok_stride + (int64_t)h * D;
+  const int sb2 = (int)(tok_stride * 2);
+  const int key0 = j * BLOCK + 64 * w;
+  // A short list's time is mostly that of the loads before its first tile: its
+  // entries first, K and V while they are under way, then the tile's rows, and
+  // the accumulators are zeroed meanwhile.
   const int p0 = tile.p0;
   int p1 = tile.p1;
-  while (p1 > p0 && rows_list[p1 - 1] >= (N + BLOCK - 1) / BLOCK) --p1;
-  const int npair = p1 - p0, T = npair * SUBS;
-
+  int cl = p1 > p0 ? rows_list[p0 + min(lane, p1 - p0 - 1)] : 0;
   f32x4 dk[8][4], dv[8][4];
+  bf16x8 kop[4][4];
+#pragma unroll
+  for (int kg = 0; kg < 4; ++kg) {
+    const __bf16* kp = K + base_bh + (int64_t)min(key0 + 16 * kg + c16, N - 1) * tok_stride + 8 * gq;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) kop[kg][ks] = *reinterpret_cast<const bf16x8*>(kp + 32 * ks);
+  }
+  int dma[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = 4 * u + (lane >> 4), p = lane & 15;
+    dma[u] = r * sb2 + 16 * ((both_off(r, p) >> 4) & 15);
+  }
+  {   // this wave's 64 rows of V (rows past N read zeros)
+    const int nrec = key0 < N ? (N - key0 - 1) * sb2 + 2 * D : 0;
+    const __amdgpu_buffer_rsrc_t rv = buffer_rsrc(V + base_bh + (int64_t)key0 * tok_stride, nrec);
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      buffer_load_lds16(rv, vblk + (w * 16 + u) * 1024, dma[u & 3] + (u >> 2) * 16 * sb2);
+  }
+  int roff[4], toff[8];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) roff[ks] = both_off(c16, 4 * ks + gq);
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) {
+    const int d = 16 * dt + 4 * (c16 & 3);
+    toff[dt] = both_off(4 * gq + (c16 >> 2), d >> 3) + 2 * (d & 7);
+  }
+  const char* const vw = vblk + w * 64 * 256;
+  while (p1 > p0 && rows_list[p1 - 1] >= (N + BLOCK - 1) / BLOCK) --p1;
+  const int npair = p1 - p0;
+  auto iof = [&](int p) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(cl, p & 63); };
+  // This wave's 16 rows of each 32-row tile: base of the query block's rows
+  // 16 w .., tile k 32 rows further each.
+  const char* const qw = reinterpret_cast<const char*>(Q + base_bh) + (int64_t)(16 * w) * sb2;
+  const char* const ow = reinterpret_cast<const char*>(dO + base_bh) + (int64_t)(16 * w) * sb2;
+  const char* const aw = reinterpret_cast<const char*>(aux + (w ? (int64_t)H * T_tok : 0) + sr.stat0);
+  struct Src { __amdgpu_buffer_rsrc_t q, o, a; };
+  auto src = [&](int i, int k) __attribute__((always_inline)) {
+    const int64_t off = (int64_t)i * ((int64_t)BLOCK * sb2) + k * (32 * sb2);
+    const int left = N - i * BLOCK - 32 * k, mine = left - 16 * w;   // rows from the tile's / this wave's first
+    const int nrec = mine > 0 ? (mine - 1) * sb2 + 2 * D : 0;
+    return Src{buffer_rsrc(qw + off, nrec), buffer_rsrc(ow + off, nrec),
+               buffer_rsrc(aw + ((int64_t)i * BLOCK + 32 * k) * 4, max(0, min(left, 32)) * 4)};
+  };
+  // direct load u of a tile: 0..3 Q, 4..7 dO, 8 statistics (one plane a wave)
+  auto load_one = [&](const Src& s, char* qd, char* od, char* ad, int u) __attribute__((always_inline)) {
+    if (u < 4) buffer_load_lds16(s.q, qd + (w * 4 + u) * 1024, dma[u]);
+    else if (u < 8) buffer_load_lds16(s.o, od + (w * 4 + u - 4) * 1024, dma[u - 4]);
+    else buffer_load_lds16(s.a, ad + w * 1024, 16 * lane);
+  };
+  const float c2 = scale * kLog2e;
+  auto rrow = [&](const char* t, int hh, int ks) __attribute__((always_inline)) {
+    return *reinterpret_cast<const bf16x8*>(t + roff[ks] + hh * 16 * 256);
+  };
+  auto rvop = [&](int kg, int ks) __attribute__((always_inline)) {
+    return *reinterpret_cast<const bf16x8*>(vw + roff[ks] + kg * 16 * 256);
+  };
+  auto rtr = [&](const char* t, int dt) __attribute__((always_inline)) {
+    const s16x4 lo = lds_read_tr16(t + toff[dt]);
+    const s16x4 hi = lds_read_tr16(t + toff[dt] + 16 * 256);
+    const s16x8 v8 = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v8);
+  };
+  // dS of the tile before, stored at the start of the next one
+  u32x4 pd[4];
+  int pos = -1, sub = 0;
+  auto store_pending = [&]() __attribute__((always_inline)) {
+    if (pos < 0) return;
+    const int g2 = ((gq & 1) << 1) | (gq >> 1);
+    char* dst = ds + (int64_t)pos * (2 * BLOCK * BLOCK) + (sub * 4 + 2 * w) * 2048 +
+                16 * (16 * g2 + (c16 ^ (4 * (g2 & 1))));
+    const bool edge = (j + 1) * BLOCK > N;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      u32x4 u0 = {pd[2 * x][0], pd[2 * x][1], pd[2 * x + 1][0], pd[2 * x + 1][1]};
+      u32x4 u1 = {pd[2 * x][2], pd[2 * x][3], pd[2 * x + 1][2], pd[2 * x + 1][3]};
+      if (edge) {
+        const int k0 = key0 + 32 * x + c16;
+        if (k0 >= N) u0[0] = u0[1] = u1[0] = u1[1] = 0u;
+        if (k0 + 16 >= N) u0[2] = u0[3] = u1[2] = u1[3] = 0u;
+      }
+      __builtin_nontemporal_store(u0, reinterpret_cast<u32x4*>(dst + x * 2048));
+      __builtin_nontemporal_store(u1, reinterpret_cast<u32x4*>(dst + x * 2048 + 1024));
+    }
+  };
+  bf16x8 ra[8];
+  constexpr int RA = 5, RV = 6;
+  f32x4 ls[2], nd[2];
+  auto read_stats = [&](const char* at) __attribute__((always_inline)) {
+    const float* const a_pl = reinterpret_cast<const float*>(at) + 4 * gq;
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      ls[hh] = *reinterpret_cast<const f32x4*>(a_pl + 16 * hh);
+      nd[hh] = *reinterpret_cast<const f32x4*>(a_pl + 256 + 16 * hh);
+    }
+  };
+  // One tile of 32 query rows; the next tile's rows load meanwhile.
+  auto iter = [&](int t, int i_n, int k_n, auto par) __attribute__((always_inline)) {
+    constexpr int P = decltype(par)::value;
+    const char* const qt = P ? q_lds1 : q_lds0;
+    const char* const ot = P ? o_lds1 : o_lds0;
+    char* const qn = P ? q_lds0 : q_lds1;
+    char* const on = P ? o_lds0 : o_lds1;
+    char* const an = P ? a_lds0 : a_lds1;
+    const Src sn = src(i_n, k_n);
+    f32x4 S[2][4], dP[2][4];
+    u32x4 pp[4];
+    bf16x8 rd[2][2], rv[8];
+    if constexpr (STORE) store_pending();
+    pin_order();
+    // P pair n (0..15): elements 2 (n & 1), +1 of quad n >> 1 (half, key group)
+    auto ppair = [&](int n) __attribute__((always_inline)) {
+      const int hh = n >> 3, kg = (n >> 1) & 3, e = 2 * (n & 1);
+      float x = __builtin_fmaf(S[hh][kg][e], c2, -ls[hh][e]);
+      float y = __builtin_fmaf(S[hh][kg][e + 1], c2, -ls[hh][e + 1]);
+      x = fast_exp2(x);
+      y = fast_exp2(y);
+      pin_value(x);
+      pin_value(y);
+      S[hh][kg][e] = x;
+      S[hh][kg][e + 1] = y;
+      unsigned q = pack_bf16x2(x, y);
+      pin_value(q);
+      pp[kg][2 * hh + (n & 1)] = q;
+    };
+    // 1: S = Q K^T
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      if (s + RA < 8) ra[(s + RA) & 7] = rrow(qt, (s + RA) >> 2, (s + RA) & 3);
+      if (s == 5) { rd[0][0] = rrow(ot, 0, 0); rd[0][1] = rrow(ot, 1, 0); }
+      if (s >= 6)
+#pragma unroll
+        for (int x = (s - 6) * RV / 2; x < (s - 5) * RV / 2; ++x) rv[x & 7] = rvop(x & 3, x >> 2);
+      const int hh = s >> 2, ks = s & 3;
+#pragma unroll
+      for (int kg = 0; kg < 4; ++kg) {
+        S[hh][kg] = mfma16(ra[s & 7], kop[kg][ks], ks == 0 ? f32x4{} : S[hh][kg]);
+        if (kg == 0 && s < 5) load_one(sn, qn, on, an, 2 * s);
+        if (kg == 2 && s < 4) load_one(sn, qn, on, an, 2 * s + 1);
+        if (kg == 1 && s >= 4) ppair(s - 4);
+        pin_order();
+      }
+    }
+    // 2: dP - delta = dO V^T - delta
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int ks = k >> 2, kg = k & 3;
+      if (k + RV < 16) rv[(k + RV) & 7] = rvop((k + RV) & 3, (k + RV) >> 2);
+      if (kg == 0 && ks < 3) { rd[(ks + 1) & 1][0] = rrow(ot, 0, ks + 1); rd[(ks + 1) & 1][1] = rrow(ot, 1, ks + 1); }
+      if (k >= 16 - RA) ra[k - 16 + RA] = rtr(ot, k - 16 + RA);
+      dP[0][kg] = mfma16(rd[ks & 1][0], rv[k & 7], ks == 0 ? nd[0] : dP[0][kg]);
+      if (k % 4 != 3) ppair(4 + k - k / 4);
+      pin_order();
+      dP[1][kg] = mfma16(rd[ks & 1][1], rv[k & 7], ks == 0 ? nd[1] : dP[1][kg]);
+      pin_order();
+    }
+    // 3: dV^T += dO^T P, and dS
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+      if (dt + RA < 8) ra[(dt + RA) & 7] = rtr(ot, dt + RA);
+      else ra[(dt + RA) & 7] = rtr(qt, dt + RA - 8);
+      const int hh = dt >> 2, kq = dt & 3;
+#pragma unroll
+      for (int kg = 0; kg < 4; ++kg) {
+        if (kg == 0) acc_mfma16<true>(dv[dt][kg], ra[dt & 7], pp[kg]);
+        else acc_mfma16<false>(dv[dt][kg], ra[dt & 7], pp[kg]);
+        if (kg == 0 || kg == 2) {
+          float x = S[hh][kq][kg] * dP[hh][kq][kg], y = S[hh][kq][kg + 1] * dP[hh][kq][kg + 1];
+          pin_value(x);
+          pin_value(y);
+          unsigned q = pack_bf16x2(x, y);
+          pin_value(q);
+          pd[kq][2 * hh + (kg >> 1)] = q;
+        }
+        pin_order();
+      }
+    }
+    // 4: dK^T += Q^T dS
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+      if (dt + RA < 8) ra[(dt + RA) & 7] = rtr(qt, dt + RA);
+      if (dt > 8 - RA) ra[(dt + RA - 1) & 7] = rrow(qn, (dt + RA - 9) >> 2, (dt + RA - 9) & 3);
+      if (dt == 9 - RA) read_stats(an);
+#pragma unroll
+      for (int kg = 0; kg < 4; ++kg) {
+        if (kg == 0) acc_mfma16<true>(dk[dt][kg], ra[dt & 7], pd[kg]);
+        else acc_mfma16<false>(dk[dt][kg], ra[dt & 7], pd[kg]);
+        pin_order();
+      }
+      if (dt == 8 - RA) {   // every read of this tile is issued
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        pin_order();
+      }
+    }
+    ra[(8 + RA - 1) & 7] = rrow(qn, (RA - 1) >> 2, (RA - 1) & 3);
+    if constexpr (STORE) {
+      const int e = p0 + t / SUBS;
+      pos = (int64_t)e < max_pairs ? e : -1;
+      sub = t % SUBS;
+    }
+  };
+  int ic = 0;
+  if (npair > 0) {
+    ic = iof(0);
+    const Src s0 = src(ic, 0);
+#pragma unroll
+    for (int u = 0; u < 9; ++u) load_one(s0, q_lds0, o_lds0, a_lds0, u);
+  }
   {
     u32x4 z = {0u, 0u, 0u, 0u};
     pin_value(z);
@@ -886,219 +1110,9 @@ __global__ __launch_bounds__(128, 1) void bwd_dkdv64_kernel(
         acc_zero16(dv[dt][kg], z);
       }
   }
-  if (T > 0) {
-    const int sb2 = (int)(tok_stride * 2);
-    const int key0 = j * BLOCK + 64 * w;
-    bf16x8 kop[4][4];
-#pragma unroll
-    for (int kg = 0; kg < 4; ++kg) {
-      const __bf16* kp = K + base_bh + (int64_t)min(key0 + 16 * kg + c16, N - 1) * tok_stride + 8 * gq;
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) kop[kg][ks] = *reinterpret_cast<const bf16x8*>(kp + 32 * ks);
-    }
-    int dma[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int r = 4 * u + (lane >> 4), p = lane & 15;
-      dma[u] = r * sb2 + 16 * ((both_off(r, p) >> 4) & 15);
-    }
-    {   // this wave's 64 rows of V (rows past N read zeros)
-      const int nrec = key0 < N ? (N - key0 - 1) * sb2 + 2 * D : 0;
-      const __amdgpu_buffer_rsrc_t rv = buffer_rsrc(V + base_bh + (int64_t)key0 * tok_stride, nrec);
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        buffer_load_lds16(rv, vblk + (w * 16 + u) * 1024, dma[u & 3] + (u >> 2) * 16 * sb2);
-    }
-    int roff[4], toff[8];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) roff[ks] = both_off(c16, 4 * ks + gq);
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) {
-      const int d = 16 * dt + 4 * (c16 & 3);
-      toff[dt] = both_off(4 * gq + (c16 >> 2), d >> 3) + 2 * (d & 7);
-    }
-    const char* const vw = vblk + w * 64 * 256;
-    int cl = rows_list[p0 + min(lane, npair - 1)];
-    auto iof = [&](int p) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(cl, p & 63); };
-    // This wave's 16 rows of each 32-row tile: base of the query block's rows
-    // 16 w .., tile k 32 rows further each.
-    const char* const qw = reinterpret_cast<const char*>(Q + base_bh) + (int64_t)(16 * w) * sb2;
-    const char* const ow = reinterpret_cast<const char*>(dO + base_bh) + (int64_t)(16 * w) * sb2;
-    const char* const aw = reinterpret_cast<const char*>(aux + (w ? (int64_t)H * T_tok : 0) + sr.stat0);
-    struct Src { __amdgpu_buffer_rsrc_t q, o, a; };
-    auto src = [&](int i, int k) __attribute__((always_inline)) {
-      const int64_t off = (int64_t)i * ((int64_t)BLOCK * sb2) + k * (32 * sb2);
-      const int left = N - i * BLOCK - 32 * k, mine = left - 16 * w;   // rows from the tile's / this wave's first
-      const int nrec = mine > 0 ? (mine - 1) * sb2 + 2 * D : 0;
-      return Src{buffer_rsrc(qw + off, nrec), buffer_rsrc(ow + off, nrec),
-                 buffer_rsrc(aw + ((int64_t)i * BLOCK + 32 * k) * 4, max(0, min(left, 32)) * 4)};
-    };
-    // direct load u of a tile: 0..3 Q, 4..7 dO, 8 statistics (one plane a wave)
-    auto load_one = [&](const Src& s, char* qd, char* od, char* ad, int u) __attribute__((always_inline)) {
-      if (u < 4) buffer_load_lds16(s.q, qd + (w * 4 + u) * 1024, dma[u]);
-      else if (u < 8) buffer_load_lds16(s.o, od + (w * 4 + u - 4) * 1024, dma[u - 4]);
-      else buffer_load_lds16(s.a, ad + w * 1024, 16 * lane);
-    };
-    const float c2 = scale * kLog2e;
-    auto rrow = [&](const char* t, int hh, int ks) __attribute__((always_inline)) {
-      return *reinterpret_cast<const bf16x8*>(t + roff[ks] + hh * 16 * 256);
-    };
-    auto rvop = [&](int kg, int ks) __attribute__((always_inline)) {
-      return *reinterpret_cast<const bf16x8*>(vw + roff[ks] + kg * 16 * 256);
-    };
-    auto rtr = [&](const char* t, int dt) __attribute__((always_inline)) {
-      const s16x4 lo = lds_read_tr16(t + toff[dt]);
-      const s16x4 hi = lds_read_tr16(t + toff[dt] + 16 * 256);
-      const s16x8 v8 = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      return __builtin_bit_cast(bf16x8, v8);
-    };
-    // dS of the tile before, stored at the start of the next one
-    u32x4 pd[4];
-    int pos = -1, sub = 0;
-    auto store_pending = [&]() __attribute__((always_inline)) {
-      if (pos < 0) return;
-      const int g2 = ((gq & 1) << 1) | (gq >> 1);
-      char* dst = ds + (int64_t)pos * (2 * BLOCK * BLOCK) + (sub * 4 + 2 * w) * 2048 +
-                  16 * (16 * g2 + (c16 ^ (4 * (g2 & 1))));
-      const bool edge = (j + 1) * BLOCK > N;
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        u32x4 u0 = {pd[2 * x][0], pd[2 * x][1], pd[2 * x + 1][0], pd[2 * x + 1][1]};
-        u32x4 u1 = {pd[2 * x][2], pd[2 * x][3], pd[2 * x + 1][2], pd[2 * x + 1][3]};
-        if (edge) {
-          const int k0 = key0 + 32 * x + c16;
-          if (k0 >= N) u0[0] = u0[1] = u1[0] = u1[1] = 0u;
-          if (k0 + 16 >= N) u0[2] = u0[3] = u1[2] = u1[3] = 0u;
-        }
-        __builtin_nontemporal_store(u0, reinterpret_cast<u32x4*>(dst + x * 2048));
-        __builtin_nontemporal_store(u1, reinterpret_cast<u32x4*>(dst + x * 2048 + 1024));
-      }
-    };
-    bf16x8 ra[8];
-    constexpr int RA = 5, RV = 6;
-    f32x4 ls[2], nd[2];
-    auto read_stats = [&](const char* at) __attribute__((always_inline)) {
-      const float* const a_pl = reinterpret_cast<const float*>(at) + 4 * gq;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        ls[hh] = *reinterpret_cast<const f32x4*>(a_pl + 16 * hh);
-        nd[hh] = *reinterpret_cast<const f32x4*>(a_pl + 256 + 16 * hh);
-      }
-    };
-    // One tile of 32 query rows; the next tile's rows load meanwhile.
-    auto iter = [&](int t, int i_n, int k_n, auto par) __attribute__((always_inline)) {
-      constexpr int P = decltype(par)::value;
-      const char* const qt = P ? q_lds1 : q_lds0;
-      const char* const ot = P ? o_lds1 : o_lds0;
-      char* const qn = P ? q_lds0 : q_lds1;
-      char* const on = P ? o_lds0 : o_lds1;
-      char* const an = P ? a_lds0 : a_lds1;
-      const Src sn = src(i_n, k_n);
-      f32x4 S[2][4], dP[2][4];
-      u32x4 pp[4];
-      bf16x8 rd[2][2], rv[8];
-      if constexpr (STORE) store_pending();
-      pin_order();
-      // P pair n (0..15): elements 2 (n & 1), +1 of quad n >> 1 (half, key group)
-      auto ppair = [&](int n) __attribute__((always_inline)) {
-        const int hh = n >> 3, kg = (n >> 1) & 3, e = 2 * (n & 1);
-        float x = __builtin_fmaf(S[hh][kg][e], c2, -ls[hh][e]);
-        float y = __builtin_fmaf(S[hh][kg][e + 1], c2, -ls[hh][e + 1]);
-        x = fast_exp2(x);
-        y = fast_exp2(y);
-        pin_value(x);
-        pin_value(y);
-        S[hh][kg][e] = x;
-        S[hh][kg][e + 1] = y;
-        unsigned q = pack_bf16x2(x, y);
-        pin_value(q);
-        pp[kg][2 * hh + (n & 1)] = q;
-      };
-      // 1: S = Q K^T
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        if (s + RA < 8) ra[(s + RA) & 7] = rrow(qt, (s + RA) >> 2, (s + RA) & 3);
-        if (s == 5) { rd[0][0] = rrow(ot, 0, 0); rd[0][1] = rrow(ot, 1, 0); }
-        if (s >= 6)
-#pragma unroll
-          for (int x = (s - 6) * RV / 2; x < (s - 5) * RV / 2; ++x) rv[x & 7] = rvop(x & 3, x >> 2);
-        const int hh = s >> 2, ks = s & 3;
-#pragma unroll
-        for (int kg = 0; kg < 4; ++kg) {
-          S[hh][kg] = mfma16(ra[s & 7], kop[kg][ks], ks == 0 ? f32x4{} : S[hh][kg]);
-          if (kg == 0 && s < 5) load_one(sn, qn, on, an, 2 * s);
-          if (kg == 2 && s < 4) load_one(sn, qn, on, an, 2 * s + 1);
-          if (kg == 1 && s >= 4) ppair(s - 4);
-          pin_order();
-        }
-      }
-      // 2: dP - delta = dO V^T - delta
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const int ks = k >> 2, kg = k & 3;
-        if (k + RV < 16) rv[(k + RV) & 7] = rvop((k + RV) & 3, (k + RV) >> 2);
-        if (kg == 0 && ks < 3) { rd[(ks + 1) & 1][0] = rrow(ot, 0, ks + 1); rd[(ks + 1) & 1][1] = rrow(ot, 1, ks + 1); }
-        if (k >= 16 - RA) ra[k - 16 + RA] = rtr(ot, k - 16 + RA);
-        dP[0][kg] = mfma16(rd[ks & 1][0], rv[k & 7], ks == 0 ? nd[0] : dP[0][kg]);
-        if (k % 4 != 3) ppair(4 + k - k / 4);
-        pin_order();
-        dP[1][kg] = mfma16(rd[ks & 1][1], rv[k & 7], ks == 0 ? nd[1] : dP[1][kg]);
-        pin_order();
-      }
-      // 3: dV^T += dO^T P, and dS
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        if (dt + RA < 8) ra[(dt + RA) & 7] = rtr(ot, dt + RA);
-        else ra[(dt + RA) & 7] = rtr(qt, dt + RA - 8);
-        const int hh = dt >> 2, kq = dt & 3;
-#pragma unroll
-        for (int kg = 0; kg < 4; ++kg) {
-          if (kg == 0) acc_mfma16<true>(dv[dt][kg], ra[dt & 7], pp[kg]);
-          else acc_mfma16<false>(dv[dt][kg], ra[dt & 7], pp[kg]);
-          if (kg == 0 || kg == 2) {
-            float x = S[hh][kq][kg] * dP[hh][kq][kg], y = S[hh][kq][kg + 1] * dP[hh][kq][kg + 1];
-            pin_value(x);
-            pin_value(y);
-            unsigned q = pack_bf16x2(x, y);
-            pin_value(q);
-            pd[kq][2 * hh + (kg >> 1)] = q;
-          }
-          pin_order();
-        }
-      }
-      // 4: dK^T += Q^T dS
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        if (dt + RA < 8) ra[(dt + RA) & 7] = rtr(qt, dt + RA);
-        if (dt > 8 - RA) ra[(dt + RA - 1) & 7] = rrow(qn, (dt + RA - 9) >> 2, (dt + RA - 9) & 3);
-        if (dt == 9 - RA) read_stats(an);
-#pragma unroll
-        for (int kg = 0; kg < 4; ++kg) {
-          if (kg == 0) acc_mfma16<true>(dk[dt][kg], ra[dt & 7], pd[kg]);
-          else acc_mfma16<false>(dk[dt][kg], ra[dt & 7], pd[kg]);
-          pin_order();
-        }
-        if (dt == 8 - RA) {   // every read of this tile is issued
-          __builtin_amdgcn_s_waitcnt(0);
-          __syncthreads();
-          pin_order();
-        }
-      }
-      ra[(8 + RA - 1) & 7] = rrow(qn, (RA - 1) >> 2, (RA - 1) & 3);
-      if constexpr (STORE) {
-        const int e = p0 + t / SUBS;
-        pos = (int64_t)e < max_pairs ? e : -1;
-        sub = t % SUBS;
-      }
-    };
-    int ic = iof(0);
-    {
-      const Src s0 = src(ic, 0);
-#pragma unroll
-      for (int u = 0; u < 9; ++u) load_one(s0, q_lds0, o_lds0, a_lds0, u);
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
+  __builtin_amdgcn_s_waitcnt(0);   // (without pairs too: V is on its way into LDS)
+  __syncthreads();
+  if (npair > 0) {
     read_stats(a_lds0);
 #pragma unroll
     for (int s = 0; s < RA; ++s) ra[s] = rrow(q_lds0, s >> 2, s & 3);
@@ -1202,7 +1216,7 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
   };
   bool wide = false;
   if constexpr (D == 128 && BLOCK == 128) {
-    wide = nrow >= kWideTiles;
+    wide = nrow >= kWideTiles && !(store && ds.max_pairs < kWideList * nrow);
     if (wide && store) dkdv(bwd_dkdv64_kernel<true>, 128);
     if (wide && !store) dkdv(bwd_dkdv64_kernel<false>, 128);
   }

@@ -20,12 +20,16 @@ DEV = "cuda"
 
 def _run(case, copies=1, **kw):
     """Gradients of `copies` samples that are all the case's one sample; the
-    64-key pass takes grids of 2,048 workgroups and more."""
+    64-key pass takes grids of 2,048 workgroups and more, with stored tiles where
+    there is room for three a list and more."""
     q, k, v, do = (case[n].to(DEV).repeat(copies, 1, 1, 1) for n in ("q", "k", "v", "do"))
     idx = ut.build_block_index(torch.from_numpy(case["block_mask"]).to(DEV).repeat(copies, 1, 1, 1))
     o, lse = ut.bsattn_fwd(q, k, v, idx, case["block"], case["scale"])
+    lists = idx["kv_colptr"].numel() - 1
     if kw.get("ds_pairs") == "half":
         kw["ds_pairs"] = idx["nnz"] // 2
+    elif kw.get("ds_pairs", None) is None:
+        kw["ds_pairs"] = max(idx["nnz"], 3 * lists)
     return ut.bsattn_bwd(q, k, v, o, do, lse, idx, case["block"], case["scale"], **kw)
 
 
@@ -61,6 +65,28 @@ def test_list_longer_than_its_registers(pairs):
     case = W.random_case(77, nb * 128 - 45, 1, 128, 128, 0.0)
     case["block_mask"][:, :, :, 1] = 1
     _check(case, _run(case, _copies(case), ds_pairs=pairs), f"pairs {pairs}")
+
+
+def test_part_of_the_tiles_in_the_64_key_pass():
+    """Room for half of the pairs, still three a list, with six lists of 131."""
+    nb = 131
+    case = W.random_case(81, nb * 128 - 77, 1, 128, 128, 0.0)
+    case["block_mask"][:, :, :, 1::25] = 1
+    _check(case, _run(case, _copies(case), ds_pairs="half"), "half of the tiles")
+
+
+@pytest.mark.parametrize("room", [2, 3])
+def test_either_side_of_the_list_length(room):
+    """2,048 workgroups with lists of one entry: with room for two tiles a list
+    they take the 32-key pass, whose bits a small grid gives too, with room for
+    three the 64-key pass."""
+    case = W.random_case(82, 200, 1, 128, 128, 0.0)
+    copies = _copies(case)
+    got = _run(case, copies, ds_pairs=room * 2 * copies)
+    _check(case, got, f"room for {room} tiles a list")
+    small = _run(case)
+    same = all(torch.equal(x[:1], y) for x, y in zip(got[1:], small[1:]))
+    assert same == (room == 2)
 
 
 @pytest.mark.parametrize("delta", [-1, 0])
