@@ -44,7 +44,9 @@ __device__ inline f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
 // such values for good, where with the builtin it moves them to VGPRs and
 // back. It does not see the instruction, so the caller keeps its hazards: two
 // wait states between a vector instruction that writes a or b and the first
-// use (wait_first puts them in), and acc_settle before c is read otherwise.
+// use (wait_first puts them in; in front of every MFMA they cost dK/dV 1 to 3%),
+// and acc_settle before c is read otherwise. tests/test_mfma_hazards.py reads the
+// built code for both, so that a compiler's copy of an operand can't go unseen.
 template <bool wait_first>
 __device__ inline void acc_mfma16(f32x4& c, bf16x8 a, u32x4 b) {
   if constexpr (wait_first)
