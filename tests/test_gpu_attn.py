@@ -20,9 +20,9 @@ DEV = "cuda"
 
 
 # dS tiles the backward's workspace makes room for: every pair (dQ from the
-# stored tiles), none (dQ recomputed) or half (the first query blocks stored,
-# the rest recomputed)
-MODES = {"stored": None, "recompute": 0, "partial": "half"}
+# stored tiles), none (dQ recomputed), half (the first query blocks stored, the
+# rest recomputed), or the helper's own choice
+MODES = {"stored": "all", "recompute": 0, "partial": "half", "default": None}
 
 
 def run_gpu(case, backward=True, ds_pairs=None):
@@ -32,10 +32,17 @@ def run_gpu(case, backward=True, ds_pairs=None):
     out = {"o": o, "lse": lse, "idx": idx}
     if backward:
         do = case["do"].to(DEV)
-        if ds_pairs == "half":
-            ds_pairs = idx["nnz"] // 2
-        out["dq"], out["dk"], out["dv"] = ut.bsattn_bwd(q, k, v, o, do, lse, idx, case["block"],
-                                                        case["scale"], ds_pairs=ds_pairs)
+        stored = ds_pairs == "all"
+        if ds_pairs in ("all", "half"):
+            ds_pairs = idx["nnz"] // (1 if stored else 2)
+        ut.ut_trace_enable(stored)
+        try:
+            out["dq"], out["dk"], out["dv"] = ut.bsattn_bwd(q, k, v, o, do, lse, idx, case["block"],
+                                                            case["scale"], ds_pairs=ds_pairs)
+            names = [t["name"] for t in ut.trace_read()] if stored else []
+        finally:
+            ut.ut_trace_enable(0)
+        assert not stored or any(nm.startswith("bwd_dq_stored") for nm in names), names
     torch.cuda.synchronize()
     return out
 

@@ -116,13 +116,13 @@ def test_non_default_stream_matches_default():
 
 
 def _dq_mode(mrng):
-    """One of the backward's dQ splits: every pair's dS tile stored (None),
-    none (0), or a random count (the rest recomputed)."""
+    """One of the backward's dQ splits: every pair's dS tile stored, none (0),
+    or a random count (the rest recomputed)."""
     m = int(mrng.integers(3))
     if m == 2:
         r = float(mrng.random())
         return "some", lambda nnz: int(r * (nnz + 1))
-    return ("all", None) if m == 0 else ("none", 0)
+    return ("all", lambda nnz: nnz) if m == 0 else ("none", 0)
 
 
 def test_random_shape_sweep():

@@ -5,7 +5,6 @@ dS tiles for part of the pairs. Against the float64 oracle (Eq. 8's gradients)
 within the tolerances of the other backward tests. Then the dQ pass that forms
 the row statistics at head_dim 64, with a gradient buffer that shares memory
 with an input."""
-import numpy as np
 import pytest
 import torch
 

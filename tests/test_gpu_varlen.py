@@ -28,16 +28,24 @@ def _dev(case):
 def _run(case, ds_pairs=None):
     q, k, v, do, cu, idx = _dev(case)
     o, lse = ut.bsattn_fwd_varlen(q, k, v, cu, case["max_seqlen"], idx, case["block"], case["scale"])
-    if ds_pairs == "half":
-        ds_pairs = idx["nnz"] // 2
-    dq, dk, dv = ut.bsattn_bwd_varlen(q, k, v, o, do, lse, cu, case["max_seqlen"], idx, case["block"],
-                                      case["scale"], ds_pairs=ds_pairs)
-    torch.cuda.synchronize()
+    stored = ds_pairs == "all"
+    if ds_pairs in ("all", "half"):
+        ds_pairs = idx["nnz"] // (1 if stored else 2)
+    ut.ut_trace_enable(stored)
+    try:
+        dq, dk, dv = ut.bsattn_bwd_varlen(q, k, v, o, do, lse, cu, case["max_seqlen"], idx,
+                                          case["block"], case["scale"], ds_pairs=ds_pairs)
+        torch.cuda.synchronize()
+        names = [t["name"] for t in ut.trace_read()] if stored else []
+    finally:
+        ut.ut_trace_enable(0)
+    assert not stored or any(nm.startswith("bwd_dq_stored") for nm in names), names
     return o, lse, dq, dk, dv
 
 
-# dS tiles in the backward's workspace: all pairs, none (dQ recomputed), half
-@pytest.mark.parametrize("ds_pairs", [None, 0, "half"])
+# dS tiles in the backward's workspace: all pairs, none (dQ recomputed), half,
+# the helper's own choice
+@pytest.mark.parametrize("ds_pairs", ["all", 0, "half", None])
 @pytest.mark.parametrize("seed,lens,H,D,block,density", [
     (1, [700, 1300, 257, 0, 128], 2, 128, 128, 0.4),
     (2, [65, 1, 300, 64], 3, 64, 64, 0.5),
