@@ -1226,15 +1226,17 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
     TraceScope ts_(s, "bwd_dq_stored", D, BLOCK);
     hipLaunchKernelGGL((bwd_dq_stored_kernel<D, BLOCK>), grid, dim3(64 * (BLOCK / 32)), 0, s,
                      bf(k), static_cast<const char*>(ds.tiles), static_cast<__bf16*>(dq), sh.N, sh.H,
-                     sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T, ds.map, ds.row_ok, by_head);
+                     sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T, ds.map, ds.row_ok,
+                     stored_dq_by_head(sh));
   }
   if (!dq_first) {
-    // every query block without row_ok (all of them without stored tiles)
+    // every query block without row_ok: all of them without stored tiles, mostly
+    // none with them (plain order, so that a workgroup ends on its first loads)
     TraceScope ts_(s, "bwd_dq", D, BLOCK);
     hipLaunchKernelGGL((bwd_dq_kernel<D, BLOCK, false>), grid, dim3(64 * (BLOCK / 32)), 0, s,
                      bf(q), bf(k), bf(v), bf(dout), aux, static_cast<__bf16*>(dq), sh.B, sh.N, sh.H,
                      sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T,
-                     store ? static_cast<const int32_t*>(ds.row_ok) : nullptr, by_head,
+                     store ? static_cast<const int32_t*>(ds.row_ok) : nullptr, by_head && !store,
                      static_cast<const __bf16*>(nullptr), static_cast<const float*>(nullptr));
   }
   return hipGetLastError();

@@ -79,6 +79,13 @@ constexpr int64_t kXcdHeadBytes = (int64_t)8 << 20;
 inline bool heads_by_xcd(const AttnShape& sh) {
   return sh.H % 8 == 0 && (int64_t)sh.N * sh.D * 4 <= kXcdHeadBytes;
 }
+// The same for dQ from the stored tiles, most of whose stream is dS tiles that
+// nothing shares. Plain / by head at block 128: 545 / 542 us at 24 x 15,000 x 128
+// and 181 / 178 at 24 x 6,552 x 128, but 1,013 / 1,053 at 24 x 22,879 x 64; at block
+// 64 1,060 / 1,164 there, 530 / 575 at 24 x 14,000 x 128 and 247 / 268 at 9,011.
+inline bool stored_dq_by_head(const AttnShape& sh) {
+  return sh.D == 128 && sh.block == 128 && heads_by_xcd(sh);
+}
 // First tile of the group of eight heads (8 nblk workgroups in a row) that
 // workgroup wg, of head wg / nblk in plain order, belongs to.
 constexpr unsigned group_tile(unsigned head, unsigned nblk) { return (head & ~7u) * nblk; }

@@ -55,6 +55,19 @@ int main() {
   two[13] = 90;   // the first group is alike, the second is not
   check("one dense head of sixteen", 141, two, false);
   check("one head with entries", 5, {0, 0, 0, 0, 0, 0, 0, 5}, false);
+  for (int i = 0; i < 4; ++i) {   // rules of the launchers: heads of at most 8 MiB, a multiple of 8
+    const int D = i & 1 ? 128 : 64, block = i & 2 ? 128 : 64;
+    const int fits = (int)(ut::kXcdHeadBytes / (4 * D));
+    const struct { int N, H; bool heads; } rules[] = {
+        {fits, 24, true}, {fits + 1, 24, false}, {1, 8, true}, {1, 12, false}, {fits, 20, false}};
+    for (const auto& r : rules) {
+      const ut::AttnShape sh{1, r.N, r.H, D, block, (r.N + block - 1) / block, 1.f};
+      const bool ok = ut::heads_by_xcd(sh) == r.heads &&
+                      ut::stored_dq_by_head(sh) == (r.heads && D == 128 && block == 128);
+      std::printf("rules: %d tokens, %d heads of %d, block %d  %s\n", r.N, r.H, D, block, ok ? "ok" : "FAIL");
+      if (!ok) ++failures;
+    }
+  }
   std::printf("%d failure(s)\n", failures);
   return failures != 0;
 }
