@@ -42,7 +42,8 @@ CASES = [  # seed, N, H, D, block, k_keep
     (9, 70000, 1, 64, 16, 300),    # 4375 blocks: one row per workgroup
     (10, 2000, 2, 96, 64, 5),      # head_dim 96: the fused multiply-add path, 16 rows per group
     (11, 900, 3, 24, 32, 3),       # head_dim 24
-    (12, 61000, 1, 128, 64, 100),  # 954 blocks, head_dim 128: past the MFMA path's LDS limit
+    (12, 61000, 1, 128, 64, 100),  # 954 blocks, head_dim 128
+    (13, 66000, 1, 128, 64, 100),  # 1,032 blocks: past the MFMA path's longest row
 ]
 
 
@@ -159,9 +160,9 @@ def _exact_qk(seed, nb, D, kind):
 
 
 @pytest.mark.parametrize("kind", ["integers", "ties", "outlier", "inf"])
-@pytest.mark.parametrize("nb,D", [(256, 128), (257, 128), (640, 128), (641, 128), (896, 128), (897, 128),
-                                  (256, 64), (257, 64), (640, 64), (641, 64), (960, 64), (961, 64),
-                                  (1025, 64), (300, 96)])
+@pytest.mark.parametrize("nb,D", [(256, 128), (257, 128), (640, 128), (641, 128), (897, 128),
+                                  (1024, 128), (1025, 128), (256, 64), (257, 64), (640, 64), (641, 64),
+                                  (961, 64), (1024, 64), (1025, 64), (300, 96)])
 def test_topk_exact_scores_at_row_lengths(nb, D, kind):
     """Either side of the row lengths where the selection's registers and
     kernels change: bit-exact against the oracle, ties lowest block first."""
