@@ -48,17 +48,17 @@ CAL_COPY_BYTES = 1 << 28      # calibration copy: 256 MiB read + 256 MiB written
 PROFILED = {
     "workload": "c2k_train", "rho": "0.1",
     "sources": {
-        "fwd": (('bsattn_fwd.hip', 'attn_util.h'), "5bbcff441148d3fa14f1c3197da865e0813d94ae047d285a669d450cd3e67de4"),
-        "bwd": (('bsattn_bwd.hip', 'attn_util.h'), "2b0de87dada004fe950c49e27856bb0c66f6a00235564bfad69d940526e8e54c"),
-        "btd": (('btd.hip',), "3693ed358fb6d91c33f658b65c20ccc9deb2b9dbfe6b9ee7cf3cdee1733fa091"),
+        "fwd": (('bsattn_fwd.hip', 'attn_util.h', 'common.h'), "b3621c626c6e593be3a040b273a84eaa190ff619210069d1d3655674ccf5ec0a"),
+        "bwd": (('bsattn_bwd.hip', 'attn_util.h', 'common.h'), "fbc4fe61805765b397830fb650879706066f905e7b944aba6bddf680d35cf822"),
+        "btd": (('btd.hip',), "8abed36cef46535a3ae231f02d7ed5f41dd050546ea8a8f8a1f5b65953a1698a"),
     },
     "kernels": {
-        "bsattn_fwd<128,128>": {"read_bytes": 4.2809e+10, "write_bytes": 4.9016e+08, "clock_ghz": 1.67, "sources": "fwd"},
-        "bwd_dkdv_store<128,128>": {"read_bytes": 5.3586e+10, "write_bytes": 2.9874e+10, "clock_ghz": 1.75, "sources": "bwd"},
-        "bwd_dq_stored<128,128>": {"read_bytes": 5.1522e+10, "write_bytes": 4.737e+08, "clock_ghz": 2.13, "sources": "bwd"},
-        "bwd_prep_map<128>": {"read_bytes": 1.0391e+09, "write_bytes": 1.0237e+08, "clock_ghz": 2.04, "sources": "bwd"},
-        "gather_rows": {"read_bytes": 4.7588e+08, "write_bytes": 4.7349e+08, "clock_ghz": 2.31, "sources": "btd"},
-        "scatter_rows": {"read_bytes": 4.7588e+08, "write_bytes": 4.7348e+08, "clock_ghz": 2.27, "sources": "btd"},
+        "bsattn_fwd<128,128>": {"read_bytes": 4.3123e+10, "write_bytes": 4.9016e+08, "clock_ghz": 1.69, "sources": "fwd"},
+        "bwd_dkdv_store<128,128>": {"read_bytes": 5.3567e+10, "write_bytes": 2.9874e+10, "clock_ghz": 1.78, "sources": "bwd"},
+        "bwd_dq_stored<128,128>": {"read_bytes": 5.1501e+10, "write_bytes": 4.7374e+08, "clock_ghz": 2.13, "sources": "bwd"},
+        "bwd_prep_map<128>": {"read_bytes": 1.0391e+09, "write_bytes": 1.0238e+08, "clock_ghz": 2.08, "sources": "bwd"},
+        "gather_rows": {"read_bytes": 4.7587e+08, "write_bytes": 4.735e+08, "clock_ghz": 2.42, "sources": "btd"},
+        "scatter_rows": {"read_bytes": 4.7588e+08, "write_bytes": 4.7348e+08, "clock_ghz": 2.41, "sources": "btd"},
     },
 }
 

@@ -166,8 +166,8 @@ ut_status ut_scatter_foreground(const void* x_packed, const int32_t* kept_idx,
  * workspace  device scratch of ut_build_block_index_workspace_size(B, H, Nq,
  *            Nk) bytes. That size is 0 for every shape: the per-row and
  *            per-column counts are written straight into q_rowptr and
- *            kv_colptr and scanned there in place, so the build needs no
- *            memory beyond its outputs. NULL with workspace_bytes = 0 is
+ *            kv_colptr and replaced by offsets in place, so the build needs
+ *            no memory beyond its outputs. NULL with workspace_bytes = 0 is
  *            valid; the arguments keep the signature uniform with the other
  *            calls that take scratch.
  * Errors: any of B, H, Nq, Nk < 1, B*H > 65535, B*H*Nq*Nk >= 2^31 (the

@@ -483,8 +483,10 @@ def _ds_pairs(index, ds_pairs, block: int, head_dim: int, base: int, device) -> 
     128, unless that would take more than half of the device memory still
     free, and none at head_dim 64, where a tile costs as many bytes but saves
     half the products: at 24 x 22,879 x 64, density 0.2, the backward takes
-    2.74 ms with stored tiles and 2.36 ms recomputing dQ (block 128; 2.91 and
-    2.58 ms at block 64; 4.11 and 4.32 ms at head_dim 128)."""
+    2.65 ms with stored tiles and 2.12 ms recomputing dQ (block 128; 2.85 and
+    2.38 ms at block 64). At head_dim 128 it takes 3.81 and 3.97 ms there, 21.6
+    and 22.0 ms at 77,060, density 0.1, 0.58 and 0.58 at 6,552, density 0.3, and
+    1.77 and 2.03 with block 64 at 14,000, density 0.2."""
     if ds_pairs is None and head_dim == 64:
         return 0
     if ds_pairs is None:

@@ -13,9 +13,9 @@
 // (one workgroup per array) instead of the sums in launch 2.
 // Launches 1 and 2 each build both kinds of list: their first workgroups take
 // a 64-column slab of one (b, h) each (column lists), the rest take 64 mask
-// rows each (row lists). Lists are put together in
-// LDS and written coalesced: a row by its wave, a slab's columns, one contiguous
-// run of the output, by the workgroup.
+// rows each (row lists). Lists are put together in LDS and written coalesced: a
+// row by its wave, a slab's columns, one contiguous run of the output, by the
+// workgroup.
 #include <hip/hip_runtime.h>
 
 #include "common.h"
@@ -32,9 +32,10 @@ static_assert(kLists == kWaves * kRowsPerWave, "row lists per workgroup");
 constexpr int kPrefixPer = 16;    // counts per thread of the sums in the fill
 // At 14,472 rows and columns (24 heads, 603 blocks, density 0.1) the sums add
 // about 4 us to the fill and save a scan launch of 7.8 us. The two launches now
-// take 8.8 + 15.3 us there (three launches, with a load per mask byte and a
-// store per 64 columns: 11.3 + 7.8 + 23.7 us); both are bound by the vector
-// instructions and the latencies of one pass over 8.7 MB, not by bandwidth.
+// take 11.7 + 15.3 us there between events (8.9 + 12.7 in a kernel trace; three
+// launches, with a load per mask byte and a store per 64 columns, between events:
+// 11.3 + 7.8 + 23.7); both are bound by the vector instructions and the latencies
+// of one pass over 8.7 MB, not by bandwidth.
 constexpr int64_t kPrefixMax = kPrefixPer * kThreads;
 // Entries (uint16) of a slab's columns that LDS holds; longer runs, and block
 // indices past 65535, are written straight to the output. Such columns are
@@ -268,9 +269,9 @@ __device__ __forceinline__ void row_lists(const uint8_t* __restrict__ mask, int6
 // column j0 + c. Wave w walks a contiguous range of 64-row tiles and gathers a
 // tile's 64 x 64 bits with 16 loads of 4 bytes per lane. The waves' counts,
 // added in wave order through LDS, place each wave's rows within its columns'
-// lists; filling then takes each lane's set bits in turn into the staged run. Lists too long for it take the columns one at a
-// time with the lanes as rows, so each column's new entries are written
-// contiguously.
+// lists; filling then takes each lane's set bits in turn into the staged run.
+// Lists too long for it take the columns one at a time with the lanes as rows, so
+// each column's new entries are written contiguously.
 template <bool kFill, bool kScanned, bool kTiny>
 __device__ __forceinline__ void col_lists(const uint8_t* __restrict__ mask, int Nq, int Nk, int32_t* colptr,
                           int32_t* __restrict__ rows_out, int64_t cap, int64_t wg, int slabs,

@@ -829,8 +829,8 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
 //   4. dK^T += Q^T dS  (32), the barrier, the next tile's first operands.
 // Measured, kernel above / this one: dense at 24 x 12,801 3.42 / 3.03 ms; with
 // the dS stores at 24 x 77,060, density 0.1, 15.4 / 14.6 ms and at
-// 24 x 22,879, density 0.2, 2.70 / 2.60. MFMA busy stays at 53% but the clock
-// rises from 1.67 to 1.82 GHz under the board's power limit (half the LDS
+// 24 x 22,879, density 0.2, 2.70 / 2.55. MFMA busy stays at 53 to 54% but the
+// clock rises from 1.67 to 1.78 GHz under the board's power limit (half the LDS
 // instructions). Operands read ahead by 3 instead of 5 groups cost 1%; waiting
 // for the loads only, not the stores, did not survive the compiler's own waits.
 // At head_dim 64 or block 64 the accumulators are half as large and the kernel

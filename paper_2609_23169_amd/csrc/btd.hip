@@ -5,9 +5,9 @@
 // Compaction works on 4 KiB mask tiles. Masks of up to kFusedTiles tiles take one
 // launch, in which every workgroup counts what lies before its tile by itself;
 // longer ones take three (count, one-workgroup scan of the tile counts, fill),
-// so any L up to 2^31 works. The result is deterministic either way. The row copies are HBM-bound: one 64-lane wave moves one row
-// with 16-byte non-temporal loads and stores, all of a row's loads in flight
-// before its stores.
+// so any L up to 2^31 works. The result is deterministic either way.
+// The row copies are HBM-bound: one 64-lane wave moves one row with 16-byte
+// non-temporal loads and stores, all of a row's loads in flight before its stores.
 #include <hip/hip_runtime.h>
 
 #include "common.h"
@@ -115,8 +115,8 @@ __global__ __launch_bounds__(kThreads) void compact_fill(const uint8_t* __restri
 // One launch: the workgroup of tile t counts the mask before the tile (16 bytes
 // a thread and 16 KiB a step, eight steps' loads in flight), then its first 256
 // threads fill the tile. The three launches it replaces took 4.7 + 4.8 + 5.7 us
-// at 52 tiles (212,992 tokens), nearly all of it launch and latency; this one
-// takes 8.6 us. Its reads grow with the square of the tiles: a call with the
+// at 52 tiles (212,992 tokens) between events, nearly all of it launch and
+// latency; this one takes 9.9 us (7.2 in a kernel trace). Its reads grow with the square of the tiles: a call with the
 // count's readback took 40.5 us with three launches and 38.4 with one at 52
 // tiles, and 41.5 and 41.8 at 123, so the line lies in between.
 constexpr int64_t kFusedTiles = 64;

@@ -102,7 +102,8 @@ __global__ __launch_bounds__(kThreads) void loss_partial_kernel(
 }
 
 // One partial sum per thread: a single wave's 16 loads in turn were most of
-// this launch's time (4.9 us; 2.3 now, 1,024 partial sums).
+// this launch's time (1,024 partial sums between two events: 6.8 us, 5.9 now; the
+// whole call at 48,000 x 128 in fp32 21.1 -> 18.2).
 __global__ __launch_bounds__(kLossParts) void loss_final_kernel(const double* __restrict__ partial,
                                                                 int parts, int64_t n, int C,
                                                                 float* __restrict__ loss) {

@@ -14,9 +14,8 @@
 //            multiply-adds otherwise, with fewer rows per workgroup when a
 //            row is long), then each wave takes one row at a time: a bisection
 //            (counts by ballot and scalar popcount) finds the k-th largest key,
-//            and the row of the mask keeps every larger key
-//            plus, of the keys equal to it, the lowest block indices up to k
-//            in total. With P prefix blocks (always-kept text tokens), the
+//            and the row of the mask keeps every larger key plus, of the keys
+//            equal to it, the lowest block indices up to k in total. With P prefix blocks (always-kept text tokens), the
 //            first P rows are dense, the first P columns are always kept, and
 //            the k best blocks are chosen among the rest.
 #include <algorithm>
@@ -224,9 +223,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 // Eight waves a SIMD up to 640 blocks (64 registers, the query rows in registers
 // and not LDS; longer rows leave room for two workgroups a CU and need more):
 // four workgroups fit a CU's LDS at 603 blocks and the 912 of 24 heads run in
-// one round. With three a CU the kernel took 80 us, with four it takes 70
-// (82 with the radix select); about 40 of them are the score products (fp32
-// matrix rate: 15) and 25 the selection.
+// one round; three a CU leave a second, nearly empty one (80 us and 70, both with
+// the interpolating search). The kernel takes 64 us there (77 with that search),
+// of which the products need 15 at the fp32 matrix rate.
 // M64: 64-key registers of a row, at least nk / 64. With by_head (heads a
 // multiple of 8) a head's workgroups run on one XCD, whose L2 then holds that
 // head's pooled keys instead of every active head's.
