@@ -15,7 +15,8 @@
 //           for P; the smaller shape draws less power per FLOP);
 //   dK/dV : one workgroup per (b, h, key block j), walking the query blocks
 //           that select j (column lists) in 32-row query tiles. At head_dim
-//           128, block 128 one wave per 64 keys, described at its kernel;
+//           128, block 128 one wave per 64 keys, described at its kernel (and a
+//           second launch for lists that are serial chains, where such can be);
 //           otherwise one wave per 32 keys (K rows in registers, the key
 //           block's V rows in LDS):
 //           S = Q K^T and dP = dO V^T (lane = key column, 32x32x16; the dP
@@ -573,13 +574,13 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dq_stored_kernel(
 // At every block size the kernel is built for two waves per SIMD (the launch
 // bound's second argument): up to 256 VGPRs per wave.
 template <int D, int BLOCK, bool STORE>
-__global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
-    const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
+__device__ __forceinline__ void dkdv_tile(
+    const Tile tile, const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     const __bf16* __restrict__ dO, const float* __restrict__ aux, __bf16* __restrict__ dK,
     __bf16* __restrict__ dV, int N_all, int H, int nblk, float scale,
-    const int32_t* __restrict__ colptr, const int32_t* __restrict__ rows_list,
+    const int32_t* __restrict__ rows_list,
     const int32_t* __restrict__ cu_seqlens, int64_t T_tok, char* __restrict__ ds,
-    int64_t max_pairs, bool by_head) {
+    int64_t max_pairs) {
   constexpr int NK = BLOCK / 32;        // key groups (one wave each)
   using C = BwdCfg<D, BLOCK, NK, 32>;
   constexpr int AUXB = 2048;            // 32 rows of each plane, one 1 KB load each
@@ -596,7 +597,6 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kw = w;   // 32-key group
   const int l32 = lane & 31, g = lane >> 5;
-  const Tile tile = tile_of(colptr, by_head, nblk);   // tile order: see the launcher
   const int j = tile.i;
   const int h = (int)(tile.bh % (unsigned)H), b = (int)(tile.bh / (unsigned)H);
   const int64_t tok_stride = (int64_t)H * D;
@@ -809,6 +809,66 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
   store_out(dV, dv16, 1.f);
 }
 
+template <int D, int BLOCK, bool STORE>
+__global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
+    const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
+    const __bf16* __restrict__ dO, const float* __restrict__ aux, __bf16* __restrict__ dK,
+    __bf16* __restrict__ dV, int N_all, int H, int nblk, float scale,
+    const int32_t* __restrict__ colptr, const int32_t* __restrict__ rows_list,
+    const int32_t* __restrict__ cu_seqlens, int64_t T_tok, char* __restrict__ ds,
+    int64_t max_pairs, bool by_head) {
+  dkdv_tile<D, BLOCK, STORE>(tile_of(colptr, by_head, nblk), Q, K, V, dO, aux, dK, dV, N_all, H, nblk,
+                             scale, rows_list, cu_seqlens, T_tok, ds, max_pairs);
+}
+
+// The same for the lists that the 64-key pass leaves to it (chain_list), fewer
+// than kMaxChains and mostly none: workgroup g collects all of them and takes the
+// one with g smaller. (A workgroup per list, each with 68 KB of LDS, would take 40
+// us to find none among 14,472; several lists in turn per workgroup made the
+// compiled loop over a list's tiles 15% slower.)
+constexpr int kMaxChains = 256;
+__global__ __launch_bounds__(256, 2) void bwd_dkdv_long_kernel(
+    const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
+    const __bf16* __restrict__ dO, const float* __restrict__ aux, __bf16* __restrict__ dK,
+    __bf16* __restrict__ dV, int N_all, int H, int nblk, float scale,
+    const int32_t* __restrict__ colptr, const int32_t* __restrict__ rows_list,
+    const int32_t* __restrict__ cu_seqlens, int64_t T_tok, char* __restrict__ ds,
+    int64_t max_pairs, unsigned lists) {
+  __shared__ int count, mine, found[kMaxChains];
+  const unsigned tid = threadIdx.x;
+  const int all = colptr[lists];
+  if (tid == 0) count = 0;
+  __syncthreads();
+  constexpr unsigned kBatch = 8;   // loads in flight
+  for (unsigned i0 = 0; i0 < lists; i0 += 256 * kBatch) {
+    int n[kBatch];
+#pragma unroll
+    for (unsigned u = 0; u < kBatch; ++u) {
+      const unsigned i = min(i0 + 256 * u + tid, lists - 1);
+      n[u] = colptr[i + 1] - colptr[i];
+    }
+#pragma unroll
+    for (unsigned u = 0; u < kBatch; ++u)
+      if (i0 + 256 * u + tid < lists && chain_list(n[u], all)) {
+        const int at = atomicAdd(&count, 1);
+        if (at < kMaxChains) found[at] = (int)(i0 + 256 * u + tid);
+      }
+  }
+  __syncthreads();
+  const int total = min(count, kMaxChains);
+  if ((int)blockIdx.x >= total) return;
+  if ((int)tid < total) {   // in any order: the rank decides
+    int smaller = 0;
+    for (int x = 0; x < total; ++x) smaller += found[x] < found[tid];
+    if (smaller == (int)blockIdx.x) mine = found[tid];
+  }
+  __syncthreads();
+  const unsigned lt = (unsigned)__builtin_amdgcn_readfirstlane(mine), bh = lt / (unsigned)nblk;
+  const Tile tile = {lt, bh, (int)(lt - bh * nblk), colptr[lt], colptr[lt + 1]};
+  dkdv_tile<128, 128, true>(tile, Q, K, V, dO, aux, dK, dV, N_all, H, nblk, scale, rows_list,
+                             cu_seqlens, T_tok, ds, max_pairs);
+}
+
 // ---------------------------------------------------------------------------
 // dK, dV at head_dim 128, block 128: one wave per 64 keys, one wave per SIMD
 // ---------------------------------------------------------------------------
@@ -845,12 +905,11 @@ __global__ __launch_bounds__(64 * (BLOCK / 32), 2) void bwd_dkdv_kernel(
 // 759 / 748 us at 22,879 tokens, 266 / 276 at 2 and 12,000. How long lists are is
 // known here from the room for their tiles only, so below kWideList tiles a list
 // the kernel above stays; without stored tiles, or with more room than the lists
-// need, lists of one or two entries cost up to 4%. A single list longer than all
-// others together keep one of the 512 places busy is a serial chain of its own,
-// twice as long here: one dense column of 179 or 602 entries among lists of three
-// in each of 12 or 4 heads takes 1,105 / 1,247 and 3,103 / 3,600 us. (The four
-// dense rows and columns of a text prefix at 24 heads are shorter than that:
-// 28.3 / 27.7 ms at 77,060 tokens and lists of 64.)
+// need, lists of one or two entries cost 2%.
+// A list that is long beside all others together is a serial chain which the rest
+// of the launch does not cover, and longer here than with 32 keys a wave: with
+// stored tiles the 32-key pass takes such lists in a launch of its own
+// (chain_list).
 constexpr int64_t kWideTiles = 2048, kWideList = 3;
 template <bool STORE>
 __global__ __launch_bounds__(128, 1) void bwd_dkdv64_kernel(
@@ -859,7 +918,7 @@ __global__ __launch_bounds__(128, 1) void bwd_dkdv64_kernel(
     __bf16* __restrict__ dV, int N_all, int H, int nblk, float scale,
     const int32_t* __restrict__ colptr, const int32_t* __restrict__ rows_list,
     const int32_t* __restrict__ cu_seqlens, int64_t T_tok, char* __restrict__ ds,
-    int64_t max_pairs, bool by_head) {
+    int64_t max_pairs, bool by_head, unsigned lists) {
   constexpr int D = 128, BLOCK = 128, TILEB = 32 * 256, SUBS = 4;
   __shared__ __attribute__((aligned(1024))) char q_lds0[TILEB];
   __shared__ __attribute__((aligned(1024))) char q_lds1[TILEB];
@@ -872,6 +931,7 @@ __global__ __launch_bounds__(128, 1) void bwd_dkdv64_kernel(
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, gq = lane >> 4;
   const Tile tile = tile_of(colptr, by_head, nblk);
+  if (lists && chain_list(tile.p1 - tile.p0, colptr[lists])) return;   // left to the 32-key pass
   const int j = tile.i;
   const int h = (int)(tile.bh % (unsigned)H), b = (int)(tile.bh / (unsigned)H);
   const int64_t tok_stride = (int64_t)H * D;
@@ -1207,21 +1267,30 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
                        dim3((unsigned)((rows_total + 255) / 256) + map_wgs), dim3(256), 0, s, bf(o),
                        bf(dout), lse, aux, sh.T, sh.N, sh.H, sh.cu != nullptr, map, map_wgs);
   }
-  auto dkdv = [&](auto kernel, int threads) {
-    TraceScope ts_(s, store ? "bwd_dkdv_store" : "bwd_dkdv", D, BLOCK);
-    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, bf(q), bf(k), bf(v), bf(dout), aux,
+  // last: by_head, or the number of lists for the 64-key pass's second launch
+  auto dkdv = [&](auto kernel, dim3 wgs, int threads, const char* name, auto... last) {
+    TraceScope ts_(s, name, D, BLOCK);
+    hipLaunchKernelGGL(kernel, wgs, dim3(threads), 0, s, bf(q), bf(k), bf(v), bf(dout), aux,
                        static_cast<__bf16*>(dk), static_cast<__bf16*>(dv), sh.N, sh.H, sh.nblk,
                        sh.scale, colptr, rows, sh.cu, sh.T, store ? ds.tiles : nullptr,
-                       store ? ds.max_pairs : (int64_t)0, by_head);
+                       store ? ds.max_pairs : (int64_t)0, last...);
   };
+  const char* const name = store ? "bwd_dkdv_store" : "bwd_dkdv";
   bool wide = false;
   if constexpr (D == 128 && BLOCK == 128) {
     wide = nrow >= kWideTiles && !(store && ds.max_pairs < kWideList * nrow);
-    if (wide && store) dkdv(bwd_dkdv64_kernel<true>, 128);
-    if (wide && !store) dkdv(bwd_dkdv64_kernel<false>, 128);
+    if (wide) {
+      // a column can only be a chain where there are few entries in all: known
+      // here from the room for their tiles, else not looked for
+      const bool chains = store && chain_list(sh.nblk, ds.max_pairs);
+      dkdv(store ? bwd_dkdv64_kernel<true> : bwd_dkdv64_kernel<false>, grid, 128, name, by_head,
+           chains ? (unsigned)nrow : 0u);
+      if (chains) dkdv(bwd_dkdv_long_kernel, dim3(kMaxChains), 256, "bwd_dkdv_long", (unsigned)nrow);
+    }
   }
-  if (!wide && store) dkdv(bwd_dkdv_kernel<D, BLOCK, true>, 64 * (BLOCK / 32));
-  if (!wide && !store) dkdv(bwd_dkdv_kernel<D, BLOCK, false>, 64 * (BLOCK / 32));
+  if (!wide)
+    dkdv(store ? bwd_dkdv_kernel<D, BLOCK, true> : bwd_dkdv_kernel<D, BLOCK, false>, grid,
+         64 * (BLOCK / 32), name, by_head);
   if (store) {
     TraceScope ts_(s, "bwd_dq_stored", D, BLOCK);
     hipLaunchKernelGGL((bwd_dq_stored_kernel<D, BLOCK>), grid, dim3(64 * (BLOCK / 32)), 0, s,

@@ -86,6 +86,15 @@ inline bool heads_by_xcd(const AttnShape& sh) {
 inline bool stored_dq_by_head(const AttnShape& sh) {
   return sh.D == 128 && sh.block == 128 && heads_by_xcd(sh);
 }
+// Whether a column list of n entries, of `all` entries in the launch, is a serial
+// chain more than twice as long as what each of the 512 workgroups that fit takes
+// (so fewer than 256 lists are). Backward with stored tiles, one dense column in
+// each head, chains with the 64-key pass / apart in ms (32-key pass for all lists):
+// 24 x 22,879, lists of 9, 2.08 / 2.06 and 2.12 / 2.06 (2.00, column 7 and 170);
+// of 3, 1.54 / 1.45 (1.40); 24 x 12,000, lists of 5, 0.911 / 0.893 (0.868);
+// 24 x 77,060, lists of 9, 7.93 / 7.44 (7.50); 4 heads, lists of 30, 5.33 / 5.00
+// (4.99). Looking for chains costs about 10 us where there are none.
+constexpr bool chain_list(int64_t n, int64_t all) { return n * 256 > all; }
 // First tile of the group of eight heads (8 nblk workgroups in a row) that
 // workgroup wg, of head wg / nblk in plain order, belongs to.
 constexpr unsigned group_tile(unsigned head, unsigned nblk) { return (head & ~7u) * nblk; }

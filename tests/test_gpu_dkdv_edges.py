@@ -56,14 +56,55 @@ def test_short_blocks(n):
     _check(case, _run(case, copies, ds_pairs=0), f"recompute n {n}")
 
 
-@pytest.mark.parametrize("pairs", [None, 0, "half"])
+@pytest.mark.parametrize("pairs", [None, 0, "half", 40000])
 def test_list_longer_than_its_registers(pairs):
     """Key block 1 is selected by all 131 query blocks (three loads of its
-    list), the others by one or two."""
+    list), the others by one or two. With room for few more tiles than pairs the
+    long lists are chains, taken apart by the 32-key pass; with room for 40,000
+    (or no tiles) the 64-key pass keeps them."""
     nb = 131
     case = W.random_case(77, nb * 128 - 45, 1, 128, 128, 0.0)
     case["block_mask"][:, :, :, 1] = 1
-    _check(case, _run(case, _copies(case), ds_pairs=pairs), f"pairs {pairs}")
+    copies = _copies(case)
+    ut.ut_trace_enable(1)
+    try:
+        grads = _run(case, copies, ds_pairs=pairs)
+        names = [t["name"] for t in ut.trace_read()]
+    finally:
+        ut.ut_trace_enable(0)
+    assert any(n.startswith("bwd_dkdv_long") for n in names) == (pairs is None), names
+    _check(case, grads, f"pairs {pairs}")
+
+
+def test_chains_beside_other_lists():
+    """Chains in some of the heads, a packed batch whose samples end before the
+    block grid does, and lists of every length below a chain's: every list is
+    taken once."""
+    lens, reps, h, nb = [90 * 128 - 5, 70 * 128 + 33], 8, 2, 90
+    case = W.varlen_case(83, lens, h, 128, 128, 0.0, garbage_past_end=False)
+    m = case["block_mask"]
+    m[0, 0, :, 17] = m[0, 1, :, 88] = m[1, 1, :70, 3] = 1   # chains
+    m[1, 0, :12, 40] = 1                                    # not one
+    q, k, v, do = (case[n].to(DEV).repeat(reps, 1, 1) for n in ("q", "k", "v", "do"))
+    cu = torch.tensor([0] + lens * reps, device=DEV).cumsum(0).to(torch.int32)
+    idx = ut.build_block_index(torch.from_numpy(m).to(DEV).repeat(reps, 1, 1, 1))
+    lists = idx["kv_colptr"].numel() - 1
+    assert lists >= 2048 and 70 * 256 > idx["nnz"] > 12 * 256
+    a = (cu, max(lens), idx, 128, case["scale"])
+    o, lse = ut.bsattn_fwd_varlen(q, k, v, *a)
+    ut.ut_trace_enable(1)
+    try:
+        got = ut.bsattn_bwd_varlen(q, k, v, o, do, lse, *a, ds_pairs=3 * lists)
+        names = [t["name"] for t in ut.trace_read()]
+    finally:
+        ut.ut_trace_enable(0)
+    assert any(n.startswith("bwd_dkdv_long") for n in names), names
+    ref = oracle.bsattn_bwd_varlen(case["q"], case["k"], case["v"], case["do"], case["cu_seqlens"], m,
+                                   128, case["scale"])
+    for x, y, nm in zip(got, ref, ("dq", "dk", "dv")):
+        x = x.reshape(reps, sum(lens), *x.shape[1:])
+        check_grad(x[0], y, nm)
+        assert torch.equal(x, x[:1].expand_as(x)), f"{nm}: copies differ"
 
 
 def test_part_of_the_tiles_in_the_64_key_pass():
