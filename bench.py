@@ -48,17 +48,17 @@ CAL_COPY_BYTES = 1 << 28      # calibration copy: 256 MiB read + 256 MiB written
 PROFILED = {
     "workload": "c2k_train", "rho": "0.1",
     "sources": {
-        "fwd": (('bsattn_fwd.hip', 'attn_util.h', 'common.h'), "b3621c626c6e593be3a040b273a84eaa190ff619210069d1d3655674ccf5ec0a"),
-        "bwd": (('bsattn_bwd.hip', 'attn_util.h', 'common.h'), "fbc4fe61805765b397830fb650879706066f905e7b944aba6bddf680d35cf822"),
+        "fwd": (('bsattn_fwd.hip', 'attn_util.h', 'common.h'), "d1ba8fc967fb7ef7eb1f269c808e146e1f2a40d8200b10a561499bc6897c49a5"),
+        "bwd": (('bsattn_bwd.hip', 'attn_util.h', 'common.h'), "ecc0eda328591d1d40342e32765eea2fc1f76ef06601d6d0cbea0984937507fd"),
         "btd": (('btd.hip',), "8abed36cef46535a3ae231f02d7ed5f41dd050546ea8a8f8a1f5b65953a1698a"),
     },
     "kernels": {
-        "bsattn_fwd<128,128>": {"read_bytes": 4.3123e+10, "write_bytes": 4.9016e+08, "clock_ghz": 1.69, "sources": "fwd"},
-        "bwd_dkdv_store<128,128>": {"read_bytes": 5.3567e+10, "write_bytes": 2.9874e+10, "clock_ghz": 1.78, "sources": "bwd"},
-        "bwd_dq_stored<128,128>": {"read_bytes": 5.1501e+10, "write_bytes": 4.7374e+08, "clock_ghz": 2.13, "sources": "bwd"},
-        "bwd_prep_map<128>": {"read_bytes": 1.0391e+09, "write_bytes": 1.0238e+08, "clock_ghz": 2.08, "sources": "bwd"},
-        "gather_rows": {"read_bytes": 4.7587e+08, "write_bytes": 4.735e+08, "clock_ghz": 2.42, "sources": "btd"},
-        "scatter_rows": {"read_bytes": 4.7588e+08, "write_bytes": 4.7348e+08, "clock_ghz": 2.41, "sources": "btd"},
+        "bsattn_fwd<128,128>": {"read_bytes": 4.3077e+10, "write_bytes": 4.9016e+08, "clock_ghz": 1.69, "sources": "fwd"},
+        "bwd_dkdv_store<128,128>": {"read_bytes": 5.3557e+10, "write_bytes": 2.9874e+10, "clock_ghz": 1.78, "sources": "bwd"},
+        "bwd_dq_stored<128,128>": {"read_bytes": 5.1524e+10, "write_bytes": 4.7373e+08, "clock_ghz": 2.11, "sources": "bwd"},
+        "bwd_prep_map<128>": {"read_bytes": 1.0391e+09, "write_bytes": 1.0238e+08, "clock_ghz": 2.06, "sources": "bwd"},
+        "gather_rows": {"read_bytes": 4.7588e+08, "write_bytes": 4.7349e+08, "clock_ghz": 2.39, "sources": "btd"},
+        "scatter_rows": {"read_bytes": 4.7588e+08, "write_bytes": 4.7348e+08, "clock_ghz": 2.38, "sources": "btd"},
     },
 }
 
