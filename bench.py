@@ -48,8 +48,8 @@ CAL_COPY_BYTES = 1 << 28      # calibration copy: 256 MiB read + 256 MiB written
 PROFILED = {
     "workload": "c2k_train", "rho": "0.1",
     "sources": {
-        "fwd": (('bsattn_fwd.hip', 'attn_util.h', 'common.h'), "d1ba8fc967fb7ef7eb1f269c808e146e1f2a40d8200b10a561499bc6897c49a5"),
-        "bwd": (('bsattn_bwd.hip', 'attn_util.h', 'common.h'), "ecc0eda328591d1d40342e32765eea2fc1f76ef06601d6d0cbea0984937507fd"),
+        "fwd": (('bsattn_fwd.hip', 'attn_util.h', 'common.h'), "74b424ac9262ecac5a088a7aa6b2d27b0b9c6ef1c3888af5f3ede7261b96dae5"),
+        "bwd": (('bsattn_bwd.hip', 'attn_util.h', 'common.h'), "4c7dce7c3415f4bcd7afa1e0196b4c51e7ea8162ed20f96872328f2626a6bed8"),
         "btd": (('btd.hip',), "8abed36cef46535a3ae231f02d7ed5f41dd050546ea8a8f8a1f5b65953a1698a"),
     },
     "kernels": {

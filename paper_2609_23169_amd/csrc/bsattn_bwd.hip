@@ -1296,7 +1296,7 @@ hipError_t launch_bwd_t(const void* q, const void* k, const void* v, const void*
     hipLaunchKernelGGL((bwd_dq_stored_kernel<D, BLOCK>), grid, dim3(64 * (BLOCK / 32)), 0, s,
                      bf(k), static_cast<const char*>(ds.tiles), static_cast<__bf16*>(dq), sh.N, sh.H,
                      sh.nblk, sh.scale, rowptr, cols, sh.cu, sh.T, ds.map, ds.row_ok,
-                     stored_dq_by_head(sh));
+                     stored_dq_by_head(sh, ds.max_pairs));
   }
   if (!dq_first) {
     // every query block without row_ok: all of them without stored tiles, mostly

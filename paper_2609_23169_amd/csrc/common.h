@@ -79,12 +79,18 @@ constexpr int64_t kXcdHeadBytes = (int64_t)8 << 20;
 inline bool heads_by_xcd(const AttnShape& sh) {
   return sh.H % 8 == 0 && (int64_t)sh.N * sh.D * 4 <= kXcdHeadBytes;
 }
-// The same for dQ from the stored tiles, most of whose stream is dS tiles that
-// nothing shares. Plain / by head at block 128: 545 / 542 us at 24 x 15,000 x 128
-// and 181 / 178 at 24 x 6,552 x 128, but 1,013 / 1,053 at 24 x 22,879 x 64; at block
-// 64 1,060 / 1,164 there, 530 / 575 at 24 x 14,000 x 128 and 247 / 268 at 9,011.
-inline bool stored_dq_by_head(const AttnShape& sh) {
-  return sh.D == 128 && sh.block == 128 && heads_by_xcd(sh);
+// The same for dQ from the stored tiles. By head an XCD reads the tiles that it
+// wrote itself, and finds them in its L2 where a head's fit: plain / by head 35 / 31
+// us at 24 x 2,000 x 128 with block 64, density 0.4 (3.4 MB of tiles a head), 75 / 71
+// at 6,000, 0.1 (7.5), 31 / 29 at 24 x 4,000 x 64, 0.1 (3.5), but 86 / 91 there at
+// 0.4 (13), 84 / 88 at 8,000, 0.1 (13), 161 / 173 at 6,000 x 64 with block 128, 0.4
+// (29) and 1,060 / 1,164 at 22,879 x 64. At head_dim 128, block 128, it is never
+// behind: 181 / 178 at 24 x 6,552 (27), 545 / 542 at 15,000 (90). `pairs`: the room
+// for tiles, which is all that is known of their number here.
+constexpr int64_t kXcdTileBytes = (int64_t)8 << 20;
+inline bool stored_dq_by_head(const AttnShape& sh, int64_t pairs) {
+  return heads_by_xcd(sh) && ((sh.D == 128 && sh.block == 128) ||
+                              pairs * 2 * sh.block * sh.block <= kXcdTileBytes * sh.B * sh.H);
 }
 // Whether a column list of n entries, of `all` entries in the launch, is a serial
 // chain more than twice as long as what each of the 512 workgroups that fit takes

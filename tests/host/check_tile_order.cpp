@@ -62,8 +62,11 @@ int main() {
         {fits, 24, true}, {fits + 1, 24, false}, {1, 8, true}, {1, 12, false}, {fits, 20, false}};
     for (const auto& r : rules) {
       const ut::AttnShape sh{1, r.N, r.H, D, block, (r.N + block - 1) / block, 1.f};
-      const bool ok = ut::heads_by_xcd(sh) == r.heads &&
-                      ut::stored_dq_by_head(sh) == (r.heads && D == 128 && block == 128);
+      // dQ from the stored tiles: also a head's tiles in 8 MiB, but at 128 / 128
+      const int64_t fit = ut::kXcdTileBytes / (2 * block * block) * r.H;
+      const bool always = D == 128 && block == 128;
+      const bool ok = ut::heads_by_xcd(sh) == r.heads && ut::stored_dq_by_head(sh, fit) == r.heads &&
+                      ut::stored_dq_by_head(sh, fit + r.H) == (r.heads && always);
       std::printf("rules: %d tokens, %d heads of %d, block %d  %s\n", r.N, r.H, D, block, ok ? "ok" : "FAIL");
       if (!ok) ++failures;
     }
